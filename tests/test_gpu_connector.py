@@ -155,6 +155,25 @@ def test_connector_deterministic_and_rowwise():
     np.testing.assert_array_equal(run(np.ascontiguousarray(x[5:6]), cw), a[5:6])
 
 
+# Row counts whose products take each block tile (32 x 32 up to 256 x 256) on
+# 4096 features with 256 compute units; the reduction of the first product is
+# one long stage, a few, or no multiple of one.
+@pytest.mark.parametrize("Dv", [64, 256, 832])
+def test_connector_rows_bits_do_not_depend_on_the_tile(Dv):
+    cw = W.connector_weights(Dv, 4096, 192, W.BF16, seed=Dv)
+    x = rows(Dv, 4100, Dv, "wide")
+    wd = weights_dev(cw)
+    xd = last.to_torch(x, cw.dtype, "cuda")
+    counts = (1, 33, 64, 65, 128, 129, 200, 257, 600, 1024, 1100, 1500, 2049, 2900, 4100)
+    full = last.connector(xd, *wd)
+    for n in counts:
+        a = 4100 - n   # the last n rows: another place in the batch too
+        assert torch.equal(last.connector(xd[a:].contiguous(), *wd), full[a:]), n
+    idx = np.array([0, 31, 32, 255, 256, 4095, 4099])
+    y, var_y, acc2 = expected(np.ascontiguousarray(x[idx]), cw)
+    assert_close(bf16_to_f64(full)[idx], y, var_y, acc2, f"Dv {Dv}")
+
+
 def test_connector_empty_and_rejections():
     cw = W.connector_weights(64, 64, 64, W.BF16, seed=3)
     out = last.connector(torch.empty((0, 64), dtype=torch.bfloat16, device="cuda"), *weights_dev(cw))
