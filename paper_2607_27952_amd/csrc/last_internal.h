@@ -129,11 +129,10 @@ constexpr int kMcSlotWords = 256;    // exchange words per request of the multi-
 
 // The k-center in rounds (rounds.hip), without the N x N matrix: candidates
 // a round, picks a round, tokens a fold task, and the largest Dv and N_r it
-// takes (its candidate-Gram chunks and select keys live in LDS).
+// takes (its select keys live in LDS).
 constexpr int kRoundCands = 192;
-constexpr int kRoundPicks = 64;
-constexpr int kRoundPairs = (kRoundCands / 32) * (kRoundCands / 32 + 1) / 2;   // 32 x 32 block pairs of the candidate Gram
-constexpr int kRoundCandTasks = kRoundPairs;                                      // one block pair a task
+constexpr int kRoundPicks = 128;
+constexpr int kRoundCandTasks = 0;    // candidate-Gram tasks of their own a round (the greedy task forms it)
 constexpr int kRoundFoldRows = 256;
 constexpr int kRoundMaxDv = 4096;
 constexpr int kRoundMaxN = 32768;
@@ -204,7 +203,6 @@ struct SelectWs {
   // the rounds form (nn and inv as above; nothing else of the matrix form)
   float *r_dl;                     // [N_total] running minimum coverage distance
   int32_t *r_cand, *r_picks;       // [R][kRoundCands], [R][kRoundPicks]
-  float *r_cmat;                   // [R][kRoundCands][kRoundCands] candidate distances
   int32_t *r_st;                   // [R][4] request state
   unsigned long long *r_T;         // [R] bound keys
   uint32_t *r_dcnt;                // [R] completed tasks

@@ -36,15 +36,23 @@
 //   k_rnorm    |x_i|^2 and 1 / |x_i| of every token (one pass over X).
 //   k_rprep    fold-tile prefixes and the per-request state.
 //   k_rounds   the rounds, as a queue of tasks on a persistent grid; per
-//              request and round: S (select the candidates), C (one 32 x 32
-//              block pair of the candidate Gram each), G (the greedy on the
-//              candidates), F (fold the picks into 256 tokens each), listed
-//              round by round and, within a round, phase by phase. A block
-//              takes the next task index from a global counter and waits
-//              until the tasks it depends on (all with smaller indices, so
-//              already taken by running blocks) have completed: no block
-//              ever waits for a block that has not started, so the grid needs
-//              no co-residency. Every wait is bounded by a wall-clock limit.
+//              request and round: S (select the candidates), G (the
+//              candidates' distances and the greedy on them), F (fold the
+//              picks into 256 tokens each), listed round by round and, within
+//              a round, phase by phase. (The task order also provides for C,
+//              kCT tasks between S and G; there are none.) A block takes the
+//              next task index from a global counter and waits until the
+//              tasks it depends on (all with smaller indices, so already taken
+//              by running blocks) have completed: no block ever waits for a
+//              block that has not started, so the grid needs no co-residency.
+//              Every wait is bounded by a wall-clock limit.
+//
+// What bounds it: the folds, which read X once a round (video batch, 8 x
+// 16384 tokens of 3584: 10.6 rounds of 128 picks, 5440 folds of 89 us on 256
+// units, 10 GB, 4.6 TB/s while folding), and the chain of one request's
+// rounds (S 23 us, G 89, F 89). Rounds of 64 picks needed 17 of them: 3.53 ms
+// against 2.53 for that batch, 10.9 against 4.7 ms for 128 ragged requests of
+// 256 to 16384 tokens (1536 wide), 1.52 against 1.01 for 32 x 2880 (4096).
 //   k_rfail    after a timeout, marks the unfinished requests invalid.
 #include <algorithm>
 #include <climits>
@@ -65,8 +73,6 @@ constexpr int kRThreads = 512;
 constexpr int kRWaves = kRThreads / 64;
 constexpr int kRB = kRoundCands;              // candidates a round at most
 constexpr int kRSub = kRB / 32;               // 32-slot blocks of the candidate list
-constexpr int kRPairs = kRoundPairs;
-static_assert(kRPairs == kRSub * (kRSub + 1) / 2, "block pairs");
 constexpr int kRP = kRoundPicks;              // picks a round at most
 constexpr int kFRows = kRoundFoldRows;        // tokens a fold task
 constexpr int kFRing = 3;                     // fold ring stages (two in flight)
@@ -75,11 +81,16 @@ constexpr int kFTokPieces = kFRows * kFCols * 2 / 16;   // 16-byte pieces of tok
 constexpr int kFPickPieces = kRP * kFCols * 2 / 16;     // ... of picks
 constexpr int kFStagePieces = kFTokPieces + kFPickPieces;
 constexpr int kFTokInstr = kFTokPieces / 64 / kRWaves;  // LDS-DMA instructions a wave, tokens
-static_assert(kFPickPieces == 64 * kRWaves, "one pick DMA instruction a wave");
-constexpr int kFPerWave = kFTokInstr + 1;
-constexpr int kMaxChunks = kRoundMaxDv / 128;
-constexpr int kCT = kRoundCandTasks;           // C tasks per request and round (one block pair each)
-static_assert(kCT == kRPairs, "C tasks");
+constexpr int kFTiles = kRP / 32;                       // 32-pick tiles of a fold task
+constexpr int kFPickInstr = kFPickPieces / 64 / kRWaves;   // ... picks, of a fold with every tile
+static_assert(kFTiles % 2 == 0 && kFPickInstr == kFTiles / 2, "a pick DMA instruction a wave per two tiles");
+constexpr int kCT = kRoundCandTasks;           // C tasks per request and round
+constexpr int kGRing = 6;                      // candidate-Gram ring stages (five in flight)
+constexpr int kGStagePieces = kRB * kFCols * 2 / 16;    // 16-byte pieces of candidates a stage
+constexpr int kGPerWave = kGStagePieces / 64 / kRWaves;  // LDS-DMA instructions a wave
+static_assert(kGPerWave * 64 * kRWaves == kGStagePieces, "even DMA split");
+constexpr int kGStride = kRB + 1;              // floats of a row of the candidate matrix (odd: its mirror
+                                               // writes, one column a lane group, spread over the banks)
 constexpr int kSelLds = kRoundMaxN;           // keys of a request held in LDS by the select
 constexpr int kFtLds = 2048;                  // fold-tile prefixes held in LDS (batches of fewer requests)
 static_assert(kRB % 64 == 0 && kRB <= 256, "candidate slots: whole waves");
@@ -150,8 +161,10 @@ __device__ __forceinline__ float coverage_ab(double dot, double nna, double nnb,
 }
 __device__ __forceinline__ float coverage_dir(int x, int y, double dot, double nnx, double nny, double invx,
                                               double invy) {
-  if (x == y) return -INFINITY;
-  return (x >> 5) <= (y >> 5) ? coverage_ab(dot, nnx, nny, invx, invy) : coverage_ab(dot, nny, nnx, invy, invx);
+  // selects only: a branch per distance costs more than the distance
+  const bool fwd = (x >> 5) <= (y >> 5);
+  const float c = coverage_ab(dot, nnx, nny, fwd ? invx : invy, fwd ? invy : invx);
+  return x == y ? -INFINITY : c;
 }
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -166,7 +179,6 @@ struct RArgs {
   float *dl;                       // [N_total] running minimum distance (+inf before the first pick, -inf once picked)
   int32_t *cand;                   // [R][kRB] this round's candidates (request-local token indices)
   int32_t *picks;                  // [R][kRP] this round's picks
-  float *cmat;                     // [R][kRB][kRB] candidate distances, row = pick slot
   int32_t *st;                     // [R][4] picks so far, picks this round, candidates, finished
   unsigned long long *st_T;        // [R] the bound key T
   uint32_t *dcnt;                  // [R] completed tasks
@@ -187,12 +199,13 @@ struct SmFold {
   int pick[kRP];
   double pnn[kRP], pinv[kRP];
 };
-struct SmCand {
-  float part[kMaxChunks][1024];   // fp32 partial sums of each 128-column chunk
-  int tok[2][32];
-};
 struct SmGreedy {
-  alignas(16) float mat[kRB * kRB];
+  union {
+    uint4 ring[kGRing][kGStagePieces];
+    float mat[kRB * kGStride];
+  };
+  double nn[kRB], inv[kRB];
+  int tok[kRB];
 };
 struct SmSelect {
   uint32_t v[kSelLds];            // key of each token: objective bits + 1, or 0
@@ -201,7 +214,6 @@ struct SmSelect {
 };
 union SmAll {
   SmFold f;
-  SmCand c;
   SmGreedy g;
   SmSelect s;
 };
@@ -594,168 +606,363 @@ __device__ void task_select(const RArgs &a, SmAll &sm, const Req &q, unsigned lo
   }
 }
 
-// C: candidate slots [32 sa, 32 sa + 32) against [32 sb, 32 sb + 32), both
-// directions. The eight waves take the 128-column chunks in turn (chunk c on
-// wave c % 8), keep each chunk's fp32 partial sums in LDS, and the chunks
-// are then added in column order in fp64, as the Gram folds them. A wave's
-// next chunk is loaded while the matrix cores work on the current one, and
-// the norms the distances need are loaded before the chunks.
-__device__ void task_cand(const RArgs &a, SmAll &sm, const Req &q, int pair) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
-  int sa = 0, rest = pair;
-  while (rest >= kRSub - sa) {
-    rest -= kRSub - sa;
-    ++sa;
-  }
-  const int sb = sa + rest;
-  const int nb = uni(ld_i32(a.st + 4 * q.r + kStNb));
-  if (32 * sb >= nb) return;
-  SmCand &c = sm.c;
-  if (tid < 64) {
-    const int side = tid >> 5, slot = (side ? sb : sa) * 32 + (tid & 31);
-    c.tok[side][tid & 31] = ld_i32(a.cand + (int64_t)q.r * kRB + min(slot, nb - 1));
-  }
-  __syncthreads();
-  // this thread's two outputs e = tid + 512 h: A row i, B column j of the
-  // 32 x 32 accumulator layout, and the norms of their tokens
-  constexpr int kOut = 1024 / kRThreads;
-  int ti[kOut], tj[kOut];
-  double nni[kOut], nnj[kOut], invi[kOut], invj[kOut];
-#pragma unroll
-  for (int h = 0; h < kOut; ++h) {
-    const int e = tid + h * kRThreads, v = e >> 6, l = e & 63;
-    ti[h] = c.tok[0][(l >> 5) * 4 + (v & 3) + 8 * (v >> 2)];
-    tj[h] = c.tok[1][l & 31];
-    nni[h] = a.nn[q.n0 + ti[h]];
-    nnj[h] = a.nn[q.n0 + tj[h]];
-    invi[h] = a.inv[q.n0 + ti[h]];
-    invj[h] = a.inv[q.n0 + tj[h]];
-  }
-  const int nc = a.Dv / 128;
-  const uint16_t *pa = a.X + (q.n0 + c.tok[0][lane & 31]) * (int64_t)a.Dv + 8 * (lane >> 5);
-  const uint16_t *pb = a.X + (q.n0 + c.tok[1][lane & 31]) * (int64_t)a.Dv + 8 * (lane >> 5);
-  auto load = [&](int ch, uint4 (&fa)[8], uint4 (&fb)[8]) {
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      fa[s] = *reinterpret_cast<const uint4 *>(pa + ch * 128 + 16 * s);
-      fb[s] = *reinterpret_cast<const uint4 *>(pb + ch * 128 + 16 * s);
-    }
-  };
-  auto product = [&](int ch, const uint4 (&fa)[8], const uint4 (&fb)[8]) {
-    f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fa[0]), as_bf16x8(fb[0]), f32x16{}, 0, 0, 0);
-#pragma unroll
-    for (int s = 1; s < 8; ++s)
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fa[s]), as_bf16x8(fb[s]), acc, 0, 0, 0);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) c.part[ch][v * 64 + lane] = acc[v];
-  };
-  // chunks wave, wave + 8, ... in two register sets, one chunk ahead
-  uint4 xa[8], xb[8], ya[8], yb[8];
-  if (wave < nc) load(wave, xa, xb);
-  for (int ch = wave; ch < nc; ch += 2 * kRWaves) {
-    const int c1 = ch + kRWaves, c2 = ch + 2 * kRWaves;
-    if (c1 < nc) load(c1, ya, yb);
-    product(ch, xa, xb);
-    if (c2 < nc) load(c2, xa, xb);
-    if (c1 < nc) product(c1, ya, yb);
-  }
-  __syncthreads();
-  float *M = a.cmat + (int64_t)q.r * kRB * kRB;
-#pragma unroll
-  for (int h = 0; h < kOut; ++h) {
-    const int e = tid + h * kRThreads, v = e >> 6, l = e & 63;
-    const int i = (l >> 5) * 4 + (v & 3) + 8 * (v >> 2), j = l & 31;   // A row, B column
-    const int si = 32 * sa + i, sj = 32 * sb + j;
-    if (si >= nb || sj >= nb) continue;
-    double dot = 0.0;
-    for (int ch = 0; ch < nc; ++ch) dot += (double)c.part[ch][e];
-    st_f32(M + (int64_t)si * kRB + sj, coverage_dir(ti[h], tj[h], dot, nni[h], nnj[h], invi[h], invj[h]));
-    if (sa != sb) st_f32(M + (int64_t)sj * kRB + si, coverage_dir(tj[h], ti[h], dot, nnj[h], nni[h], invj[h], invi[h]));
-  }
-}
-
-// G: the greedy of Eq. 9-11 on the candidates while each pick is certified
-// (its key above T), at most kRP picks. Wave 0 runs it; three slots a lane.
+// G: the candidates' mutual distances, then the greedy of Eq. 9-11 on them
+// while each pick is certified (its key above T), at most kRP picks.
+//
+// The distances: the upper triangle of the kRB x kRB Gram in 32 x 32 blocks
+// on the matrix cores, both directions of every pair, into LDS. The
+// candidates' rows stream through an LDS ring (LDS DMA, 64 columns a stage);
+// wave w owns up to three blocks of one block row or column, in the Gram's
+// 128-column chunks folded into fp64. One block forms the whole matrix, so
+// it never leaves LDS: as 21 tasks of one block each, the pairs cost a
+// dequeue and a wait apiece and the matrix a round trip through memory
+// (ragged batch of 128 requests: 16400 such tasks, 27 us each with the waits,
+// 1.7 of 7.5 ms).
 __device__ void task_greedy(const RArgs &a, SmAll &sm, const Req &q) {
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const int nb = uni(ld_i32(a.st + 4 * q.r + kStNb));
   if (nb == 0) return;
   SmGreedy &g = sm.g;
-  const float *M = a.cmat + (int64_t)q.r * kRB * kRB;
-  // rows 0..nb-1 whole (columns past nb are never read), two floats a load,
-  // eight loads in flight
-  const int ne = nb * kRB / 2;
-  const unsigned long long *M2 = reinterpret_cast<const unsigned long long *>(M);
-  unsigned long long *mat2 = reinterpret_cast<unsigned long long *>(g.mat);
-  for (int x0 = tid; x0 < ne; x0 += 8 * kRThreads) {
-    unsigned long long v[8];
+  if (tid < kRB) {
+    // slots past nb repeat the last candidate; their distances are not used
+    const int p = ld_i32(a.cand + (int64_t)q.r * kRB + min(tid, nb - 1));
+    g.tok[tid] = p;
+    g.nn[tid] = a.nn[q.n0 + p];
+    g.inv[tid] = a.inv[q.n0 + p];
+  }
+  __syncthreads();
+  {
+    const int Dv = a.Dv, nst = Dv / kFCols;   // even
+    uint32_t dst[kGPerWave], voff[kGPerWave];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = x0 + u * kRThreads < ne ? ld_u64(M2 + x0 + u * kRThreads) : 0ull;
+    for (int x = 0; x < kGPerWave; ++x) {
+      const int slot = (wave + kRWaves * x) * 64 + lane, row = slot >> 3, piece = (slot & 7) ^ ((row >> 1) & 7);
+      dst[x] = __builtin_amdgcn_readfirstlane(lds_u32(&g.ring[0][(wave + kRWaves * x) * 64]));
+      voff[x] = (uint32_t)(((int64_t)g.tok[row] * Dv + piece * 8) * 2);
+    }
+    const char *base = (const char *)uniform_ptr(a.X + q.n0 * (int64_t)Dv);
+    auto issue = [&](int st) {
+      const uint32_t add = (uint32_t)(st % kGRing) * (kGStagePieces * 16);
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (x0 + u * kRThreads < ne) mat2[x0 + u * kRThreads] = v[u];
+      for (int x = 0; x < kGPerWave; ++x) dma16(dst[x] + add, base + (int64_t)st * kFCols * 2, voff[x]);
+    };
+    // Blocks (sa, sb), sa <= sb < 6, three a wave (the last wave none of its
+    // third), as one A block row against three B block rows: wave 0 (0; 0 1 2),
+    // 1 (0; 3 4 5), 2 (1; 1 2 3), 3 (2; 2 3 4), 4 (3; 3 4 5), 5 (5; 1 2 5),
+    // 6 (4; 1 4 5), 7: none. Wave 5's first two and wave 6's first are the
+    // mirrors of (1, 5), (2, 5) and (1, 4): the product of a pair of rows is
+    // the same number either way round.
+    static_assert(kRSub == 6 && kRWaves == 8, "the blocks of a wave");
+    const int ra = wave < 2 ? 0 : wave < 5 ? wave - 1 : wave == 5 ? 5 : 4;
+    const int rb[3] = {wave == 0 ? 0 : wave == 1 || wave == 4 ? 3 : wave == 3 ? 2 : 1,
+                       wave == 0 ? 1 : wave == 1 || wave == 4 || wave == 6 ? 4 : wave == 3 ? 3 : 2,
+                       wave == 0 ? 2 : wave == 2 ? 3 : wave == 3 ? 4 : 5};
+    const bool works = wave < 7;
+    int aslot[4], bslot[4];   // of block row 0; block row x is 256 x pieces on
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int c = lane & 31, sl = c * 8 + ((2 * s + (lane >> 5)) ^ ((c >> 1) & 7));
+      aslot[s] = 256 * ra + sl;
+      bslot[s] = sl;
+    }
+    double acc64[3][16];
+    f32x16 acc[3];
+#pragma unroll
+    for (int x = 0; x < 3; ++x)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc64[x][v] = 0.0;
+#pragma unroll
+    for (int st = 0; st < kGRing - 1; ++st)
+      if (st < nst) issue(st);
+    for (int st = 0; st < nst; st += 2) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        // stage st + h has landed; the barrier publishes it and retires every
+        // read of the slot that is filled next
+        if (st + h + kGRing - 2 < nst)
+          vm_wait<(kGRing - 2) * kGPerWave>();
+        else
+          vm_wait<0>();
+        __syncthreads();
+        if (st + h + kGRing - 1 < nst) issue(st + h + kGRing - 1);
+        const uint4 *ring = g.ring[(st + h) % kGRing];
+        if (works) {
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const bf16x8 fa = as_bf16x8(ring[aslot[s]]);
+#pragma unroll
+            for (int x = 0; x < 3; ++x)
+              acc[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, as_bf16x8(ring[bslot[s] + 256 * rb[x]]),
+                                                               (h == 0 && s == 0) ? f32x16{} : acc[x], 0, 0, 0);
+          }
+        }
+      }
+      if (works) {
+#pragma unroll
+        for (int x = 0; x < 3; ++x)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc64[x][v] += (double)acc[x][v];
+      }
+    }
+    __syncthreads();   // the ring is free: the matrix takes its place
+    if (works) {
+#pragma unroll
+      for (int x = 0; x < 3; ++x) {
+        const int sj = 32 * rb[x] + (lane & 31), tj = g.tok[sj];
+        const double nnj = g.nn[sj], invj = g.inv[sj];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int si = 32 * ra + (lane >> 5) * 4 + (v & 3) + 8 * (v >> 2), ti = g.tok[si];
+          const double nni = g.nn[si], invi = g.inv[si];
+          const float c = coverage_dir(ti, tj, acc64[x][v], nni, nnj, invi, invj);
+          g.mat[si * kGStride + sj] = c;
+          if (ra != rb[x]) {
+            // the two directions differ only inside one 32-row block of X
+            float m = c;
+            if (__any((ti >> 5) == (tj >> 5))) m = coverage_dir(tj, ti, acc64[x][v], nnj, nni, invj, invi);
+            g.mat[sj * kGStride + si] = m;
+          }
+        }
+      }
+    }
   }
   __syncthreads();
   if (wave != 0) return;
   constexpr int E = kRB / 64;
   const unsigned long long T = uni64(ld_u64(a.st_T + q.r));
-  int t = uni(ld_i32(a.st + 4 * q.r + kStT));
+  const int t = uni(ld_i32(a.st + 4 * q.r + kStT));
   int np = 0;
-  int tok[E];
   float w[E], d[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int c = lane + 64 * e;
     const bool in = c < nb;
-    tok[e] = in ? ld_i32(a.cand + (int64_t)q.r * kRB + c) : 0;
-    w[e] = in ? clean_score(a.scores[q.n0 + tok[e]]) : 0.f;
-    d[e] = in ? ld_f32(a.dl + q.n0 + tok[e]) : -INFINITY;
+    const int tok = g.tok[c];
+    w[e] = in ? clean_score(a.scores[q.n0 + tok]) : 0.f;
+    d[e] = in ? ld_f32(a.dl + q.n0 + tok) : -INFINITY;
   }
+  // One wave, one dependent step a pick, so the chain is kept short.
+  // Objectives are compared as floats (a picked token's -inf or NaN counts
+  // as 0). Candidates are listed by ascending index, so the lowest index
+  // among equal objectives is the lowest slot, and the token itself is
+  // needed only when a best objective equals the bound's. Pick p of the round
+  // is kept by lane p % 64 (of two) as a slot; all are stored at the end.
+  static_assert(kRP <= 128 && E == 3, "two picks and three slots a lane");
+  const uint32_t Thi = (uint32_t)(T >> 32);
+  int ps[2] = {0, 0};
+  float pg[2] = {0.f, 0.f};
   for (;;) {
-    unsigned long long key[E], best = 0ull;
+    float o[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const float o = w[e] * d[e];   // Eq. 11
-      key[e] = o >= 0.f ? ((unsigned long long)__float_as_uint(o) << 32) | (0xFFFFFFFFu - (unsigned)tok[e]) : 0ull;
-      best = key[e] > best ? key[e] : best;
-    }
-    const unsigned long long kb = wave_max_key((uint32_t)(best >> 32), (uint32_t)best);
-    if ((kb >> 32) == 0ull || kb <= T) break;   // not certified (or the degenerate end)
-    int slot = 0;
-#pragma unroll
-    for (int e = E - 1; e >= 0; --e) {
-      const unsigned long long m = __ballot(key[e] == kb);
-      if (m) slot = (int)__ffsll((long long)m) - 1 + 64 * e;
-    }
-    const int j = (int)(0xFFFFFFFFu - (uint32_t)kb);
-    if (lane == 0) {
-      a.order[q.k0 + t] = j;
-      a.gains[q.k0 + t] = __uint_as_float((uint32_t)(kb >> 32));
-      st_f32(a.dl + q.n0 + j, -INFINITY);
-      st_i32(a.picks + (int64_t)q.r * kRP + np, j);
-    }
-    ++t;
+    for (int e = 0; e < E; ++e) o[e] = w[e] * d[e];   // Eq. 11
+    const float best = fmaxf(fmaxf(o[0], o[1]), fmaxf(o[2], 0.f));
+    const float mb = wave_max(best);
+    const uint32_t mbits = __float_as_uint(mb);
+    if (mbits == 0u || mbits < Thi) break;   // the degenerate end, or not certified
+    const unsigned long long m0 = __ballot(o[0] == mb), m1 = __ballot(o[1] == mb), m2 = __ballot(o[2] == mb);
+    const unsigned long long ms = m0 ? m0 : m1 ? m1 : m2;
+    const int slot = (int)__ffsll((long long)ms) - 1 + (m0 ? 0 : m1 ? 64 : 128);
+    if (mbits == Thi && (0xFFFFFFFFu - (unsigned)uni(g.tok[slot])) <= (uint32_t)T) break;   // not certified
+    const bool mine = lane == (np & 63), low = np < 64;
+    ps[0] = mine && low ? slot : ps[0];
+    pg[0] = mine && low ? mb : pg[0];
+    ps[1] = mine && !low ? slot : ps[1];
+    pg[1] = mine && !low ? mb : pg[1];
     ++np;
-    if (t >= q.K || np >= kRP) break;
+    if (t + np >= q.K || np >= kRP) break;
+    const float *row = g.mat + slot * kGStride + lane;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int c = lane + 64 * e;
-      if (c < nb) d[e] = fminf(d[e], g.mat[slot * kRB + c]);   // Eq. 10
+    for (int e = 0; e < E; ++e) d[e] = fminf(d[e], row[64 * e]);   // Eq. 10 (slots past nb keep -inf)
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int x = lane + 64 * h;
+    if (x < np) {
+      const int j = g.tok[ps[h]];
+      a.order[q.k0 + t + x] = j;
+      a.gains[q.k0 + t + x] = pg[h];
+      st_f32(a.dl + q.n0 + j, -INFINITY);
+      st_i32(a.picks + (int64_t)q.r * kRP + x, j);
     }
   }
   if (lane == 0) {
-    st_i32(a.st + 4 * q.r + kStT, t);
+    st_i32(a.st + 4 * q.r + kStT, t + np);
     st_i32(a.st + 4 * q.r + kStNp, np);
   }
 }
 
 // F: fold the round's picks into delta of tokens [kFRows f, kFRows f + kFRows):
-// a kFRows x kRP product (tokens x picks) on the matrix cores, both operands
-// streamed through an LDS ring by LDS DMA, 64 columns a stage; each wave
-// owns 32 tokens against one or two 32-pick tiles.
-__device__ void task_fold(const RArgs &a, SmAll &sm, const Req &q, int f) {
+// a kFRows x (32 NT) product (tokens x picks) on the matrix cores, both
+// operands streamed through an LDS ring by LDS DMA, 64 columns a stage; each
+// wave owns 32 tokens against the NT 32-pick tiles. Bound by the token rows,
+// which every round reads again: so a round takes as many picks as the
+// accumulators hold (fp32 and fp64 of 32 x 128 a wave).
+template <int NT>
+__device__ __forceinline__ void fold_tiles(const RArgs &a, SmFold &F, const Req &q, int f) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int kPick = NT / 2;                  // pick DMA instructions a wave and stage
+  constexpr int kPerWave = kFTokInstr + kPick;
+  const int i0 = f * kFRows;
+  const int nrows = min(kFRows, q.N - i0);
+  const int Dv = a.Dv;
+
+  // DMA: token instructions x < kFTokInstr cover slots (wave + 8 x) * 64 + lane
+  // (rows 0..255); pick instruction y covers slots (wave + 8 y) * 64 + lane of
+  // the pick part. Slot = row * 8 + (piece ^ ((row >> 1) & 7)).
+  constexpr uint32_t kStageBytes = kFStagePieces * 16;
+  uint32_t dst[kPerWave], voff[kPerWave];
+#pragma unroll
+  for (int x = 0; x < kFTokInstr; ++x) {
+    const int slot = (wave + kRWaves * x) * 64 + lane, row = slot >> 3, piece = (slot & 7) ^ ((row >> 1) & 7);
+    dst[x] = __builtin_amdgcn_readfirstlane(lds_u32(&F.ring[0][(wave + kRWaves * x) * 64]));
+    voff[x] = (uint32_t)(((int64_t)min(row, nrows - 1) * Dv + piece * 8) * 2);
+  }
+#pragma unroll
+  for (int y = 0; y < kPick; ++y) {
+    const int slot = (wave + kRWaves * y) * 64 + lane, row = slot >> 3, piece = (slot & 7) ^ ((row >> 1) & 7);
+    dst[kFTokInstr + y] =
+        __builtin_amdgcn_readfirstlane(lds_u32(&F.ring[0][kFTokPieces + (wave + kRWaves * y) * 64]));
+    voff[kFTokInstr + y] = (uint32_t)(((int64_t)F.pick[row] * Dv + piece * 8) * 2);
+  }
+  const char *tokbase = (const char *)uniform_ptr(a.X + (q.n0 + i0) * (int64_t)Dv);
+  const char *pickbase = (const char *)uniform_ptr(a.X + q.n0 * (int64_t)Dv);
+  const int nst = Dv / kFCols;   // even
+  auto issue = [&](int st) {
+    const uint32_t add = (uint32_t)(st % kFRing) * kStageBytes;
+#pragma unroll
+    for (int x = 0; x < kFTokInstr; ++x) dma16_nt(dst[x] + add, tokbase + (int64_t)st * kFCols * 2, voff[x]);
+#pragma unroll
+    for (int y = kFTokInstr; y < kPerWave; ++y) dma16(dst[y] + add, pickbase + (int64_t)st * kFCols * 2, voff[y]);
+  };
+
+  // Fragment slots: a row's piece is 2 s + lane / 32, XOR (row / 2) % 8; the
+  // rows of a tile are 32 apart, so every tile's slot is the first one's plus
+  // 256 (the XOR does not change).
+  int aslot[4], bslot[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const int piece = 2 * s + (lane >> 5), c = lane & 31;
+    const int sl = c * 8 + (piece ^ ((c >> 1) & 7));
+    aslot[s] = 32 * wave * 8 + sl;
+    bslot[s] = kFTokPieces + sl;
+  }
+
+  double acc64[NT][16];
+#pragma unroll
+  for (int tn = 0; tn < NT; ++tn)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc64[tn][v] = 0.0;
+  f32x16 acc[NT];
+
+  issue(0);
+  if (nst > 1) issue(1);
+  for (int st = 0; st < nst; st += 2) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (st + h + 1 < nst)
+        vm_wait<kPerWave>();
+      else
+        vm_wait<0>();
+      __syncthreads();
+      if (st + h + 2 < nst) issue(st + h + 2);
+      const uint4 *ring = F.ring[(st + h) % kFRing];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const bf16x8 fa = as_bf16x8(ring[aslot[s]]);
+#pragma unroll
+        for (int tn = 0; tn < NT; ++tn)
+          acc[tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, as_bf16x8(ring[bslot[s] + 256 * tn]),
+                                                            (h == 0 && s == 0) ? f32x16{} : acc[tn], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int tn = 0; tn < NT; ++tn)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc64[tn][v] += (double)acc[tn][v];
+  }
+
+  // distances, their minimum over the picks (lanes of a half hold one pick
+  // column each), and the fold into delta (Eq. 10). Rows past the end repeat
+  // the last one (not stored), and pick slots past np the last pick (folding
+  // it twice changes nothing).
+  int pk[NT];
+  double pnn[NT], pinv[NT];
+#pragma unroll
+  for (int tn = 0; tn < NT; ++tn) {
+    const int k = 32 * tn + (lane & 31);
+    pk[tn] = F.pick[k];
+    pnn[tn] = F.pnn[k];
+    pinv[tn] = F.pinv[k];
+  }
+  const int il0 = 32 * wave + (lane >> 5) * 4;
+  float m[16];
+  // Where no token's norm equals a pick's (no duplicate of a pick, no pick
+  // itself) and all are finite, a distance is max(0, 1 - dot inv inv) alone
+  // (a zero row has inv 0, so 1), and its minimum over the picks that of the
+  // largest product: 4 operations a pair instead of 15.
+  bool special = false;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const double nni = a.nn[q.n0 + i0 + min(il0 + (v & 3) + 8 * (v >> 2), nrows - 1)];
+    special |= !(nni < (double)INFINITY);
+#pragma unroll
+    for (int tn = 0; tn < NT; ++tn) special |= nni == pnn[tn];
+  }
+#pragma unroll
+  for (int tn = 0; tn < NT; ++tn) special |= !(pnn[tn] < (double)INFINITY);
+  if (!__any(special)) {
+    bool fwd[NT];   // the pick's 32-row block of X is not above the wave's tokens'
+#pragma unroll
+    for (int tn = 0; tn < NT; ++tn) fwd[tn] = (pk[tn] >> 5) <= (i0 >> 5) + wave;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const double invi = a.inv[q.n0 + i0 + min(il0 + (v & 3) + 8 * (v >> 2), nrows - 1)];
+      double u = 0.0;
+#pragma unroll
+      for (int tn = 0; tn < NT; ++tn) {
+        const double t = acc64[tn][v] * (fwd[tn] ? pinv[tn] : invi) * (fwd[tn] ? invi : pinv[tn]);
+        u = tn == 0 ? t : fmax(u, t);
+      }
+      const double c = 1.0 - u;
+      m[v] = c > 0.0 ? (float)c : 0.0f;
+    }
+  } else {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int i = i0 + min(il0 + (v & 3) + 8 * (v >> 2), nrows - 1);
+      const double nni = a.nn[q.n0 + i], invi = a.inv[q.n0 + i];
+      float mv = INFINITY;
+#pragma unroll
+      for (int tn = 0; tn < NT; ++tn)
+        mv = fminf(mv, coverage_dir(pk[tn], i, acc64[tn][v], pnn[tn], nni, pinv[tn], invi));
+      m[v] = mv;
+    }
+  }
+  // the minimum over the 32 lanes, each step halving the values a lane keeps
+  // (bit 4 of the lane chooses rows 8.., bit 3 rows 4.. of those, and so on)
+#pragma unroll
+  for (int w = 8, o = 16; w >= 1; w >>= 1, o >>= 1) {
+    const bool up = (lane & o) != 0;
+#pragma unroll
+    for (int v = 0; v < w; ++v) {
+      const float keep = up ? m[v + w] : m[v], give = up ? m[v] : m[v + w];
+      m[v] = fminf(keep, __shfl_xor(give, o));
+    }
+  }
+  const float mv = fminf(m[0], __shfl_xor(m[0], 1));
+  if ((lane & 1) == 0) {
+    const int vs = (lane >> 1) & 15;   // bits 4..1 of the lane, as the steps above chose them
+    const int il = il0 + (vs & 3) + 8 * (vs >> 2);
+    if (il < nrows) {
+      float *p = a.dl + q.n0 + i0 + il;
+      st_f32(p, fminf(ld_f32(p), mv));
+    }
+  }
+}
+
+__device__ void task_fold(const RArgs &a, SmAll &sm, const Req &q, int f) {
+  const int tid = threadIdx.x;
   const int t = uni(ld_i32(a.st + 4 * q.r + kStT));
   if (t >= q.K) return;   // the last round's picks need no fold (they are marked)
   const int np = uni(ld_i32(a.st + 4 * q.r + kStNp));
@@ -768,122 +975,10 @@ __device__ void task_fold(const RArgs &a, SmAll &sm, const Req &q, int f) {
     F.pinv[tid] = a.inv[q.n0 + p];
   }
   __syncthreads();
-  const int i0 = f * kFRows;
-  const int nrows = min(kFRows, q.N - i0);
-  const int Dv = a.Dv;
-  const int ntn = np > 32 ? 2 : 1;
-
-  // DMA: token instructions x < kFTokInstr cover slots (wave + 8 x) * 64 + lane
-  // (rows 0..255); the pick instruction covers slots wave * 64 + lane of the
-  // pick part (rows 0..63). Slot = row * 8 + (piece ^ ((row >> 1) & 7)).
-  constexpr uint32_t kStageBytes = kFStagePieces * 16;
-  uint32_t dst[kFPerWave], voff[kFPerWave];
-#pragma unroll
-  for (int x = 0; x < kFTokInstr; ++x) {
-    const int slot = (wave + kRWaves * x) * 64 + lane, row = slot >> 3, piece = (slot & 7) ^ ((row >> 1) & 7);
-    dst[x] = __builtin_amdgcn_readfirstlane(lds_u32(&F.ring[0][(wave + kRWaves * x) * 64]));
-    voff[x] = (uint32_t)(((int64_t)min(row, nrows - 1) * Dv + piece * 8) * 2);
-  }
-  {
-    const int slot = wave * 64 + lane, row = slot >> 3, piece = (slot & 7) ^ ((row >> 1) & 7);
-    dst[kFTokInstr] = __builtin_amdgcn_readfirstlane(lds_u32(&F.ring[0][kFTokPieces + wave * 64]));
-    voff[kFTokInstr] = (uint32_t)(((int64_t)F.pick[row] * Dv + piece * 8) * 2);
-  }
-  const char *tokbase = (const char *)uniform_ptr(a.X + (q.n0 + i0) * (int64_t)Dv);
-  const char *pickbase = (const char *)uniform_ptr(a.X + q.n0 * (int64_t)Dv);
-  const int nst = Dv / kFCols;   // even
-  auto issue = [&](int st) {
-    const uint32_t add = (uint32_t)(st % kFRing) * kStageBytes;
-#pragma unroll
-    for (int x = 0; x < kFTokInstr; ++x) dma16_nt(dst[x] + add, tokbase + (int64_t)st * kFCols * 2, voff[x]);
-    dma16(dst[kFTokInstr] + add, pickbase + (int64_t)st * kFCols * 2, voff[kFTokInstr]);
-  };
-
-  int aslot[4], bslot[2][4];
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const int piece = 2 * s + (lane >> 5);
-    const int row = 32 * wave + (lane & 31);
-    aslot[s] = row * 8 + (piece ^ ((row >> 1) & 7));
-#pragma unroll
-    for (int tn = 0; tn < 2; ++tn) {
-      const int prow = 32 * tn + (lane & 31);
-      bslot[tn][s] = kFTokPieces + prow * 8 + (piece ^ ((prow >> 1) & 7));
-    }
-  }
-
-  double acc64[2][16];
-#pragma unroll
-  for (int tn = 0; tn < 2; ++tn)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc64[tn][v] = 0.0;
-  f32x16 acc[2] = {f32x16{}, f32x16{}};
-
-  issue(0);
-  if (nst > 1) issue(1);
-  for (int st = 0; st < nst; ++st) {
-    if (st + 1 < nst)
-      vm_wait<kFPerWave>();
-    else
-      vm_wait<0>();
-    __syncthreads();
-    if (st + 2 < nst) issue(st + 2);
-    const uint4 *ring = F.ring[st % kFRing];
-    const bool fresh = (st & 1) == 0;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const bf16x8 fa = as_bf16x8(ring[aslot[s]]);
-      const bf16x8 fb0 = as_bf16x8(ring[bslot[0][s]]);
-      acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb0, (fresh && s == 0) ? f32x16{} : acc[0], 0, 0, 0);
-      if (ntn > 1) {
-        const bf16x8 fb1 = as_bf16x8(ring[bslot[1][s]]);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb1, (fresh && s == 0) ? f32x16{} : acc[1], 0, 0, 0);
-      }
-    }
-    if (st & 1) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc64[0][v] += (double)acc[0][v];
-      if (ntn > 1)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc64[1][v] += (double)acc[1][v];
-    }
-  }
-
-  // distances, their minimum over the picks (lanes of a half hold one pick
-  // column each), and the fold into delta (Eq. 10)
-  float m[16];
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int il = 32 * wave + (lane >> 5) * 4 + (v & 3) + 8 * (v >> 2);
-    const int i = i0 + il;
-    const bool iok = il < nrows;
-    const double nni = iok ? a.nn[q.n0 + i] : 1.0, invi = iok ? a.inv[q.n0 + i] : 1.0;
-    float mv = INFINITY;
-#pragma unroll
-    for (int tn = 0; tn < 2; ++tn) {
-      const int k = 32 * tn + (lane & 31);
-      if (tn < ntn && k < np && iok) {
-        const int p = F.pick[k];
-        mv = fminf(mv, coverage_dir(p, i, acc64[tn][v], F.pnn[k], nni, F.pinv[k], invi));
-      }
-    }
-    m[v] = mv;
-  }
-#pragma unroll
-  for (int o = 1; o < 32; o <<= 1)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) m[v] = fminf(m[v], __shfl_xor(m[v], o));
-  if ((lane & 31) < 16) {
-    const int vs = lane & 15;
-    float mv = m[0];
-#pragma unroll
-    for (int v = 1; v < 16; ++v) mv = v == vs ? m[v] : mv;
-    const int il = 32 * wave + (lane >> 5) * 4 + (vs & 3) + 8 * (vs >> 2);
-    if (il < nrows) {
-      float *p = a.dl + q.n0 + i0 + il;
-      st_f32(p, fminf(ld_f32(p), mv));
-    }
-  }
+  if (np > 64)
+    fold_tiles<kFTiles>(a, F, q, f);
+  else
+    fold_tiles<2>(a, F, q, f);
 }
 
 // ------------------------------------------------------------- the rounds
@@ -932,10 +1027,10 @@ __device__ __forceinline__ int64_t decode_task(int64_t u, int64_t R, Ft ft, int 
     return -1;
   }
   x -= hB;
-  if (x < RA * kCT) {
+  if (kCT > 0 && x < RA * kCT) {
     kind = 1;
-    r = (int)(x / kCT);
-    sub = (int)(x % kCT);
+    r = (int)(x / (kCT > 0 ? kCT : 1));
+    sub = (int)(x % (kCT > 0 ? kCT : 1));
     return 0;
   }
   x -= RA * kCT;
@@ -961,10 +1056,10 @@ __device__ __forceinline__ int64_t decode_task(int64_t u, int64_t R, Ft ft, int 
     return 0;
   }
   x -= hA;
-  if (x < RB * kCT) {
+  if (kCT > 0 && x < RB * kCT) {
     kind = 1;
-    r = (int)(RA + x / kCT);
-    sub = (int)(x % kCT);
+    r = (int)(RA + x / (kCT > 0 ? kCT : 1));
+    sub = (int)(x % (kCT > 0 ? kCT : 1));
     return 0;
   }
   x -= RB * kCT;
@@ -982,7 +1077,7 @@ __global__ __launch_bounds__(kRThreads) void k_rounds(RArgs a) {
   __shared__ SmAll sm;
   __shared__ unsigned long long shk[kRWaves];
   __shared__ int shi[kRWaves];
-  __shared__ int s_task[4];   // status (0 run, 1 skip, 2 exit, 3 no task), request, kind, sub-index
+  __shared__ int s_task[4];   // status (0 run, 2 exit), request, kind, sub-index
   __shared__ int s_ft[kFtLds];   // fold-tile prefixes of batches of fewer than kFtLds requests
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = uni(tid >> 6);
@@ -993,60 +1088,74 @@ __global__ __launch_bounds__(kRThreads) void k_rounds(RArgs a) {
   int prev = -1;   // the request of the task this block has just completed
   for (;;) {
     // Wave 0 publishes the completed task (every wave waited for its stores
-    // before the last barrier) and takes the next one; all its lanes poll
-    // the same words, so its branches stay uniform.
+    // before the last barrier) and takes the next one, passing over those of
+    // finished requests; all its lanes poll the same words, so its branches
+    // stay uniform. The words of one step are loaded together: each load goes
+    // to the device's coherence point, about a microsecond away.
     if (wave == 0) {
-      unsigned long long qi = 0ull;
-      if (lane == 0) {
-        if (prev >= 0) __hip_atomic_fetch_add(a.dcnt + prev, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        qi = __hip_atomic_fetch_add(a.head, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      qi = uni64(qi);
+      if (lane == 0 && prev >= 0)
+        __hip_atomic_fetch_add(a.dcnt + prev, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       int status = 0, r = 0, kind = 0, sub = 0;
-      const unsigned long long ctl = uni64(ld_u64(a.ctl));   // live requests | abort word << 32
-      if ((ctl >> 32) != 0ull || (uint32_t)ctl == 0u) {
-        status = 2;
-      } else {
+      do {
+        unsigned long long qi = 0ull;
+        if (lane == 0) qi = __hip_atomic_fetch_add(a.head, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        unsigned long long ctl = ld_u64(a.ctl);   // live requests | abort word << 32
+        qi = uni64(qi);
+        ctl = uni64(ctl);
+        status = 0;
+        if ((ctl >> 32) != 0ull || (uint32_t)ctl == 0u) {
+          status = 2;
+          break;
+        }
         const int64_t m = (int64_t)(qi / (unsigned long long)a.Q);   // macro-round
         const int64_t u = (int64_t)qi - m * a.Q;
         if (m > a.max_rounds) {
-          // every request ends by round K_r, and a block runs at most one
-          // task ahead of the others: an index this far means a fault
+          // every request ends by round K_r, and a block runs at most two
+          // tasks ahead of the others: an index this far means a fault
           if (lane == 0) st_u32(a.abort_word, 1u);
           status = 2;
-        } else {
-          const int64_t tq = decode_task(u, a.R, ft_at, kind, r, sub);
-          const int64_t n = m + tq;   // tq = -1: B's folds of the previous round
-          const int64_t tiles = ft_at(r + 1) - ft_at(r);
-          const int64_t c = 2 + kCT + tiles;
-          const int64_t need = n * c + (kind == 0 ? 0 : kind == 1 ? 1 : kind == 2 ? 1 + kCT : 2 + kCT);
-          if (n < 0) {
-            status = 3;   // B's folds before its first round: no task (nothing to publish)
-          } else if (uni(ld_i32(a.st + 4 * r + kStFin)) != 0) {
-            status = 1;
-          } else {
-            const uint64_t t0 = wall_clock64();
-            for (;;) {
-              if ((int64_t)uniu(ld_u32(a.dcnt + r)) >= need) break;
-              if (uni(ld_i32(a.st + 4 * r + kStFin)) != 0) {
-                status = 1;
-                break;
-              }
-              if (uniu(ld_u32(a.abort_word)) != 0u) {
-                status = 2;
-                break;
-              }
-              if ((int64_t)(wall_clock64() - t0) > a.limit) {
-                if (lane == 0) st_u32(a.abort_word, 1u);
-                status = 2;
-                break;
-              }
-              __builtin_amdgcn_s_sleep(1);
-            }
-            if (status == 0 && uni(ld_i32(a.st + 4 * r + kStFin)) != 0) status = 1;
-          }
+          break;
         }
-      }
+        const int64_t tq = decode_task(u, a.R, ft_at, kind, r, sub);
+        const int64_t n = m + tq;   // tq = -1: B's folds of the previous round
+        if (n < 0) {
+          status = 1;   // B's folds before its first round: no task
+          continue;
+        }
+        const int64_t tiles = ft_at(r + 1) - ft_at(r);
+        const int64_t c = 2 + kCT + tiles;
+        const int64_t need = n * c + (kind == 0 ? 0 : kind == 1 ? 1 : kind == 2 ? 1 + kCT : 2 + kCT);
+        const uint64_t t0 = wall_clock64();
+        for (;;) {
+          uint32_t done = ld_u32(a.dcnt + r);
+          int fin = ld_i32(a.st + 4 * r + kStFin);
+          uint32_t ab = ld_u32(a.abort_word);
+          done = uniu(done);
+          fin = uni(fin);
+          ab = uniu(ab);
+          if (fin != 0) {
+            status = 1;   // finished: nothing waits for its counts any more
+            break;
+          }
+          if ((int64_t)done >= need) {
+            // The loads above may be served out of order: read the end mark
+            // again now that the counts are there. A fold needs no second
+            // look (it returns when the picks are complete).
+            if (kind != 3 && uni(ld_i32(a.st + 4 * r + kStFin)) != 0) status = 1;
+            break;
+          }
+          if (ab != 0u) {
+            status = 2;
+            break;
+          }
+          if ((int64_t)(wall_clock64() - t0) > a.limit) {
+            if (lane == 0) st_u32(a.abort_word, 1u);
+            status = 2;
+            break;
+          }
+          __builtin_amdgcn_s_sleep(1);
+        }
+      } while (status == 1);
       if (lane == 0) {
         s_task[0] = status;
         s_task[1] = r;
@@ -1059,26 +1168,22 @@ __global__ __launch_bounds__(kRThreads) void k_rounds(RArgs a) {
     if (status == 2) break;
     const int r = uni(s_task[1]), kind = uni(s_task[2]), sub = uni(s_task[3]);
     __syncthreads();
-    if (status == 0) {
-      Req q;
-      q.r = r;
-      q.n0 = uni(a.cu_vis[r]);
-      q.N = uni(a.cu_vis[r + 1]) - (int)q.n0;
-      q.k0 = uni(a.cu_keep[r]);
-      q.K = uni(a.cu_keep[r + 1]) - (int)q.k0;
-      if (kind == 0)
-        task_select(a, sm, q, shk, shi);
-      else if (kind == 1)
-        task_cand(a, sm, q, sub);
-      else if (kind == 2)
-        task_greedy(a, sm, q);
-      else
-        task_fold(a, sm, q, sub);
-    }
+    Req q;
+    q.r = r;
+    q.n0 = uni(a.cu_vis[r]);
+    q.N = uni(a.cu_vis[r + 1]) - (int)q.n0;
+    q.k0 = uni(a.cu_keep[r]);
+    q.K = uni(a.cu_keep[r + 1]) - (int)q.k0;
+    if (kind == 0)
+      task_select(a, sm, q, shk, shi);
+    else if (kind == 2)
+      task_greedy(a, sm, q);
+    else
+      task_fold(a, sm, q, sub);
     // this task's stores are complete before wave 0 publishes it
     vm_wait<0>();
     __syncthreads();
-    prev = status == 3 ? -1 : r;
+    prev = r;
   }
 }
 
@@ -1134,7 +1239,6 @@ hipError_t launch_round_pick(int32_t R, int32_t Dv, const SelectPlan &p, const S
   a.dl = w.r_dl;
   a.cand = w.r_cand;
   a.picks = w.r_picks;
-  a.cmat = w.r_cmat;
   a.st = w.r_st;
   a.st_T = w.r_T;
   a.dcnt = w.r_dcnt;
@@ -1148,8 +1252,8 @@ hipError_t launch_round_pick(int32_t R, int32_t Dv, const SelectPlan &p, const S
   const int grid = std::max(1, device_cus());
   // macro-rounds: at most K_max + 1 rounds per request, one more for the
   // second half's last folds, plus those the blocks can be ahead of the last
-  // one (each holds one task)
-  a.max_rounds = (int)std::min<int64_t>(INT_MAX / 2, p.K_max + 4 + (grid + Q - 1) / Q);
+  // one (each holds one task and may take one more before it sees the end)
+  a.max_rounds = (int)std::min<int64_t>(INT_MAX / 2, p.K_max + 4 + (2 * (int64_t)grid + Q - 1) / Q);
   a.Q = Q;
   a.limit = device_wall_khz() * wait_us / 1000;
   launch_begin("rounds", s);

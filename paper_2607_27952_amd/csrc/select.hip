@@ -1005,7 +1005,6 @@ SelectWs carve_select_ws(void *ws, int32_t R, const SelectPlan &p, last_sel_mode
     w.r_dl = cv.take<float>(p.N_total);
     w.r_cand = cv.take<int32_t>((int64_t)R * kRoundCands);
     w.r_picks = cv.take<int32_t>((int64_t)R * kRoundPicks);
-    w.r_cmat = cv.take<float>((int64_t)R * kRoundCands * kRoundCands);
     w.r_st = cv.take<int32_t>((int64_t)R * 4);
     w.r_T = cv.take<unsigned long long>(R);
     w.r_dcnt = cv.take<uint32_t>(R);

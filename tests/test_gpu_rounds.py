@@ -255,3 +255,24 @@ def test_rounds_two_host_threads():
     assert not errors, errors
     for i in range(2):
         assert len(results[i]) == 4 and all(x == alone[i] for x in results[i]), f"thread {i} differs"
+
+
+@pytest.mark.parametrize("N,K,Dv", [(600, 200, 512), (257, 140, 256), (1300, 400, 1024)])
+def test_rounds_special_rows(N, K, Dv):
+    """Rows a fold cannot take by its short form (1 - dot inv inv alone): bitwise
+    duplicates of picks, zero rows, infinite and NaN rows and rows whose squared
+    norm leaves fp32; with rounds of up to 128 picks (peaked relevance)."""
+    rng = np.random.default_rng(N)
+    X = rng.standard_normal((3 * N, Dv)).astype(np.float32)
+    for r in range(3):
+        x = X[r * N:(r + 1) * N]
+        x[rng.choice(N, N // 5, replace=False)] = x[rng.choice(N, N // 5)]
+        x[rng.choice(N, 7, replace=False)] = 0.0
+        x[rng.choice(N, 3, replace=False)] *= 1e25 if r else 1e-25
+        if r == 2:
+            x[5, 3], x[40, 7], x[200] = np.inf, np.nan, -np.inf
+    w = np.exp(rng.standard_normal(3 * N) * 1.5).astype(np.float32)
+    cv, ck = (np.arange(4) * N).astype(np.int32), (np.arange(4) * K).astype(np.int32)
+    feats = last.to_torch(np.ascontiguousarray(torch.from_numpy(X).bfloat16().view(torch.int16).numpy().view(np.uint16)),
+                          W.BF16, "cuda")
+    both(feats, torch.from_numpy(w).cuda(), cv, ck, f"special rows {N}")
