@@ -239,10 +239,14 @@ size_t diverse_select_workspace(int32_t R, const int32_t *cu_vis_h, int32_t Dv,
  *                N_r <= 32768): only the distances to the tokens picked (the
  *                paper's O(K N d_v) form, about 20 bytes of workspace per
  *                token and 2 KB per request), computed for up to 128 picks at
- *                a time; the picks of a round are certified exact against every
- *                token outside its 192 candidates.
+ *                a time; the picks of a round are certified exact against
+ *                every token outside its 192 candidates.
  *              By default the rounds take batches whose every request has
- *              8192 tokens or more and the shapes above; the environment
+ *              8192 tokens or more and the shapes above, and other batches
+ *              of those shapes where an estimate from the sizes and budgets
+ *              says they are faster (the workspace is then still the
+ *              matrix's, as the query, which knows no budgets, says); the
+ *              environment
  *              variable LAST_KCENTER_FORM=gram or =rounds forces one (rounds
  *              only where those shapes allow). The rounds run as a queue of
  *              tasks on one block per compute unit in which no block waits

@@ -410,14 +410,14 @@ static size_t select_ws_bytes(int32_t R, const SelectPlan &p, last_sel_mode mode
 size_t diverse_select_workspace(int32_t R, const int32_t *cu_vis_h, int32_t Dv, last_dtype fdtype,
                                 last_sel_mode mode) {
   if (check_select(R, cu_vis_h, Dv, fdtype, mode, nullptr) != LAST_OK) return 0;
-  // The budgets change neither the form nor the workspace; plan with K_r = N_r.
-  const SelectPlan p = make_select_plan(R, cu_vis_h, cu_vis_h, mode, Dv, fdtype, false, true);
+  // The budgets do not change the workspace (kRoundsByShape); plan with K_r = N_r.
+  const SelectPlan p = make_select_plan(R, cu_vis_h, cu_vis_h, mode, Dv, fdtype, false, kRoundsByShape);
   return select_ws_bytes(R, p, mode);
 }
 
 size_t diverse_select_similarity_workspace(int32_t R, const int32_t *cu_vis_h, int32_t Dv, last_dtype fdtype) {
   if (check_select(R, cu_vis_h, Dv, fdtype, LAST_SEL_KCENTER, nullptr) != LAST_OK) return 0;
-  const SelectPlan p = make_select_plan(R, cu_vis_h, cu_vis_h, LAST_SEL_KCENTER, Dv, fdtype, false, false);
+  const SelectPlan p = make_select_plan(R, cu_vis_h, cu_vis_h, LAST_SEL_KCENTER, Dv, fdtype, false, kRoundsNever);
   return select_ws_bytes(R, p, LAST_SEL_KCENTER);
 }
 
@@ -431,8 +431,10 @@ last_status diverse_select(int32_t R, int32_t Dv, last_dtype fdtype, last_sel_mo
   if (st != LAST_OK) return st;
   if (!scores || !feats || !cu_vis || !cu_keep || !kept) return LAST_ERR_INVALID;
   if (!aligned(feats, 16)) return LAST_ERR_INVALID;
-  const SelectPlan p = make_select_plan(R, cu_vis_h, cu_keep_h, mode, Dv, fdtype, true, true);
-  const size_t need = select_ws_bytes(R, p, mode);
+  const SelectPlan p = make_select_plan(R, cu_vis_h, cu_keep_h, mode, Dv, fdtype, true, kRoundsAny);
+  size_t need = select_ws_bytes(R, p, mode);
+  if (p.rounds_by_budget)   // the query's answer, whatever the budgets
+    need = std::max(need, diverse_select_workspace(R, cu_vis_h, Dv, fdtype, mode));
   if (!ws || ws_bytes < need || !aligned(ws, 256)) return LAST_ERR_WORKSPACE;
   size_t used = 0;
   const SelectWs w = carve_select_ws(ws, R, p, mode, &used);
@@ -449,7 +451,7 @@ last_status diverse_select(int32_t R, int32_t Dv, last_dtype fdtype, last_sel_mo
 // (R, cu_vis_h, Dv, fdtype) give the same layout in both calls.
 static last_status kcenter_ws(int32_t R, const int32_t *cu_vis_h, int32_t Dv, last_dtype fdtype,
                               void *ws, size_t ws_bytes, SelectPlan *p, SelectWs *w) {
-  *p = make_select_plan(R, cu_vis_h, cu_vis_h, LAST_SEL_KCENTER, Dv, fdtype, false, false);
+  *p = make_select_plan(R, cu_vis_h, cu_vis_h, LAST_SEL_KCENTER, Dv, fdtype, false, kRoundsNever);
   const size_t need = select_ws_bytes(R, *p, LAST_SEL_KCENTER);
   if (!ws || ws_bytes < need || !aligned(ws, 256)) return LAST_ERR_WORKSPACE;
   size_t used = 0;

@@ -137,8 +137,7 @@ constexpr int kRoundFoldRows = 256;
 constexpr int kRoundMaxDv = 4096;
 constexpr int kRoundMaxN = 32768;
 // diverse_select takes the rounds by default when every request has at least
-// this many tokens (measured: the matrix form is faster on batches with
-// shorter requests)
+// this many tokens; other batches by the estimate in select.hip
 constexpr int kRoundAutoN = 8192;
 
 // A request's coverage matrix is stored as nb x nb tiles of 128 x 128 floats
@@ -188,6 +187,7 @@ struct SelectPlan {
   int32_t group_threads[kMaxGroups], group_ept[kMaxGroups];  // greedy shape per group
   int32_t group_slices[kMaxGroups];
   bool rounds;             // the k-center in rounds (rounds.hip) instead of the matrix
+  bool rounds_by_budget;   // ... by the estimate: the workspace is still the matrix form's
   int64_t round_Q;         // tasks a round of the rounds kernel
 };
 
@@ -214,10 +214,13 @@ struct SelectWs {
 // two-call form keeps one group, so both of its calls see the same plan); Dv
 // enters that schedule's cost model. allow_rounds: the k-center may run in
 // rounds (single calls only: the pick call of the two-call form has no
-// features); whether it does depends on the shapes and LAST_KCENTER_FORM.
+// features): kRoundsNever; kRoundsByShape where LAST_KCENTER_FORM or the
+// sizes alone say so, whatever the budgets (the workspace query, which has
+// none); kRoundsAny also where the estimate with the budgets says so.
+enum RoundsRule { kRoundsNever = 0, kRoundsByShape = 1, kRoundsAny = 2 };
 SelectPlan make_select_plan(int32_t R, const int32_t *cu_vis_h, const int32_t *cu_keep_h,
                             last_sel_mode mode, int32_t Dv, last_dtype fdtype, bool allow_groups,
-                            bool allow_rounds);
+                            RoundsRule rounds);
 // The rounds form: the shapes it takes, the norms (the first half, features
 // only), and the rounds themselves.
 bool rounds_supported(int32_t N_max, int32_t Dv, last_dtype fdtype);

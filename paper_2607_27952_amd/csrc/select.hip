@@ -781,20 +781,61 @@ static void greedy_shape(int32_t n, int32_t nreq, int32_t budget, int32_t *threa
 
 // The k-center's form: the matrix (gram.hip + the greedy here) or the rounds
 // (rounds.hip). LAST_KCENTER_FORM=gram or =rounds, read at every call, forces
-// one (rounds only where rounds_supported); by default the rounds take
-// batches whose every request has kRoundAutoN tokens or more.
-static bool want_rounds(int32_t N_min, int32_t N_max, int32_t Dv, last_dtype fdtype) {
-  if (!rounds_supported(N_max, Dv, fdtype)) return false;
+// one (rounds only where rounds_supported). By default the rounds take every
+// batch whose requests all have kRoundAutoN tokens or more, and others where
+// rounds_estimate says so.
+//
+// The estimate (microseconds, 256 compute units) weighs what each form does:
+//   matrix: N_r^2 / 2 distances as Gram tiles of 0.8 us per 64 columns + 3
+//     us, then K_r dependent steps of 0.6 us + 0.11 us per 1000 tokens;
+//   rounds: K_r / 128 certified rounds if every round took its 128 picks,
+//     1.1 to 2 times that as the relevance goes from peaked to uniform (1.9
+//     is used). A round folds each 256-token tile (12 us + 19.5 us per 1000
+//     columns, all units busy), and a request's rounds follow one another,
+//     each a chain of select, candidate distances, greedy and fold.
+// Fitted on uniform batches of 256 to 16384 tokens, 1 to 128 requests, three
+// widths, both kinds of relevance (deviation about 25%); the rounds are taken
+// at 0.9 of the matrix's estimate. Measured either side (matrix / rounds,
+// us): 32 x 2880 tokens, 4096 wide, 1/9 kept: 1941 / 1127 (uniform relevance
+// 1973); 64 x 576: 245 / 417; 8 x 4096, 3584 wide, 1/16: 988 / 741 (1461
+// uniform); 128 ragged requests of 256 to 16384, 1536 wide, 1/8: 12980 /
+// 4960. A larger budget needs more rounds and the same matrix, so the form
+// depends on the budgets, and the workspace is the matrix form's.
+static bool rounds_estimate(int32_t R, const int32_t *cu_vis_h, const int32_t *cu_keep_h, int32_t Dv) {
+  double tiles = 0, folds = 0, chain = 0, greedy = 0, N_max = 0;
+  const double fold_us = 12 + 0.0195 * Dv;
+  for (int r = 0; r < R; ++r) {
+    const double N = cu_vis_h[r + 1] - cu_vis_h[r], K = cu_keep_h[r + 1] - cu_keep_h[r];
+    const double nb = ceil(N / kTile), rounds = 1 + 1.9 * K / kRoundPicks;
+    N_max = std::max(N_max, N);
+    tiles += nb * (nb - 1) / 2;
+    greedy = std::max(greedy, K * (0.6 + 1.1e-4 * N));
+    folds += ceil(N / kRoundFoldRows) * rounds;
+    chain = std::max(chain, rounds * (42 + N / 1300 + 0.012 * Dv + 0.25 * std::min<double>(kRoundPicks, K) + fold_us));
+  }
+  const double cus = device_cus(), gram = tiles * (0.8 * Dv / 64 + 3) / cus, fold = folds * fold_us / cus;
+  // a ragged batch's greedies run beside the rest of its Gram: about half is hidden
+  const bool ragged = N_max > 2.0 * cu_vis_h[R] / R;
+  const double matrix = gram + greedy * std::max(1.0, R / cus) * (ragged ? 0.5 : 1.0);
+  return std::max(fold, chain) + 0.35 * std::min(fold, chain) < 0.9 * matrix;
+}
+
+static bool want_rounds(RoundsRule rule, int32_t R, const int32_t *cu_vis_h, const int32_t *cu_keep_h, int32_t N_min,
+                        int32_t N_max, int32_t Dv, last_dtype fdtype, bool *by_budget) {
+  *by_budget = false;
+  if (rule == kRoundsNever || !rounds_supported(N_max, Dv, fdtype)) return false;
   if (const char *env = getenv("LAST_KCENTER_FORM")) {
     if (strcmp(env, "gram") == 0) return false;
     if (strcmp(env, "rounds") == 0) return true;
   }
-  return N_min >= kRoundAutoN;
+  if (N_min >= kRoundAutoN) return true;
+  *by_budget = rule == kRoundsAny && rounds_estimate(R, cu_vis_h, cu_keep_h, Dv);
+  return *by_budget;
 }
 
 SelectPlan make_select_plan(int32_t R, const int32_t *cu_vis_h, const int32_t *cu_keep_h,
                             last_sel_mode mode, int32_t Dv, last_dtype fdtype, bool allow_groups,
-                            bool allow_rounds) {
+                            RoundsRule rounds) {
   SelectPlan p{};
   p.N_total = cu_vis_h[R];
   p.K_total = cu_keep_h[R];
@@ -822,7 +863,8 @@ SelectPlan make_select_plan(int32_t R, const int32_t *cu_vis_h, const int32_t *c
   p.group_slices[0] = p.g_slices;
   int32_t N_min = p.N_max;
   for (int r = 0; r < R; ++r) N_min = std::min<int32_t>(N_min, cu_vis_h[r + 1] - cu_vis_h[r]);
-  if (allow_rounds && mode == LAST_SEL_KCENTER && want_rounds(N_min, p.N_max, Dv, fdtype)) {
+  if (mode == LAST_SEL_KCENTER &&
+      want_rounds(rounds, R, cu_vis_h, cu_keep_h, N_min, p.N_max, Dv, fdtype, &p.rounds_by_budget)) {
     p.rounds = true;
     for (int r = 0; r < R; ++r)
       p.round_Q += kRoundCandTasks + 2 + (cu_vis_h[r + 1] - cu_vis_h[r] + kRoundFoldRows - 1) / kRoundFoldRows;

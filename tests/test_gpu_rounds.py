@@ -276,3 +276,31 @@ def test_rounds_special_rows(N, K, Dv):
     feats = last.to_torch(np.ascontiguousarray(torch.from_numpy(X).bfloat16().view(torch.int16).numpy().view(np.uint16)),
                           W.BF16, "cuda")
     both(feats, torch.from_numpy(w).cuda(), cv, ck, f"special rows {N}")
+
+
+@pytest.mark.parametrize("R,lo,hi,Dv", [(48, 1500, 2500, 1024), (20, 300, 8000, 768)])
+def test_default_form_depends_on_the_budgets(R, lo, hi, Dv):
+    """A batch of shorter requests takes the rounds for a small budget and the
+    matrix for a large one, on the workspace of the query (the matrix form's)
+    either way, with the bits of the matrix form; less workspace is refused."""
+    rng = np.random.default_rng(R)
+    n = rng.integers(lo, hi + 1, R)
+    cv = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    feats = torch.randn((int(cv[-1]), Dv), device="cuda", generator=torch.Generator("cuda").manual_seed(R)).bfloat16()
+    w = torch.from_numpy(np.exp(rng.standard_normal(int(cv[-1]))).astype(np.float32)).cuda()
+    for share, form in ((16, "rounds"), (1, "gram")):
+        ck = np.concatenate([[0], np.cumsum(np.maximum(1, n // share))]).astype(np.int32)
+        ws = torch.empty(last.select_workspace(cv, Dv), dtype=torch.uint8, device="cuda")
+        os.environ.pop("LAST_KCENTER_FORM", None)
+        last.profile_reset()
+        last.profile_enable(True)
+        k, o, g = last.diverse_select(w, feats, cv, ck, ws=ws)
+        torch.cuda.synchronize()
+        took = {name for name, (count, _) in last.profile_collect().items() if count}
+        last.profile_enable(False)
+        assert form in took, took
+        for a, b in zip((k, o, g), select("gram", feats, w, cv, ck)):
+            assert np.array_equal(a.cpu().numpy().view(np.uint32), b.view(np.uint32))
+        with pytest.raises(last.LastError) as e:
+            last.diverse_select(w, feats, cv, ck, ws=ws[:-256])
+        assert e.value.status == last.LAST_ERR_WORKSPACE
