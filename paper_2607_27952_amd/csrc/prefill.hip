@@ -32,11 +32,20 @@
 //                  the permutation above makes each lane's probabilities
 //                  exactly the keys its half of the B operand needs.
 // The softmax runs online per lane in base-2 units (the scale times log2 e
-// folded into the exponent's fma): the stage's row max and sum take one
-// exchange with the partner lane, and the lane's O^T column is rescaled in
-// place when some lane's max has moved.
+// folded into the exponent's fma) against a per-query reference that is the
+// first unit's largest logit and moves only when a unit's terms pass 2^64, so
+// the common path has no maximum, no exchange between lanes and no rescaling.
+//
+// What bounds it: the matrix cores at the clock the part's power allows. The
+// loop is pipelined by units of 32 keys (logits of the next unit and values
+// of the previous one on the matrix cores while the vector ALU forms this
+// one's probabilities). 8 x 16512 tokens, 28/4 heads, one layer: 23.5 ms with
+// the stage-serial loop, 14.7 now (1.07 PFLOP/s at 1.8 GHz, where torch's
+// 8192^3 product reaches 1.22); without the bank
+// swizzle below, 16.5. 64 x 640 tokens, 32 heads, 2 layers: 1.26 -> 0.87 ms.
 #include <algorithm>
 #include <math.h>
+#include <type_traits>
 
 #include "last_internal.h"
 
@@ -47,32 +56,35 @@ namespace {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-constexpr int kWaves = 4;
-constexpr int kThreads = 64 * kWaves;
-constexpr int kQB = 32 * kWaves;              // query positions per block
-constexpr int kKS = 64;                       // keys per LDS stage
+constexpr int kKS = 64;                       // keys per LDS stage: two units of 32
 constexpr float kLog2e = 1.4426950408889634f;
+// The sum of one unit's terms past which a query's reference moves.
+constexpr float kMoveAt = 0x1p64f;
+
+constexpr int kNW = 4;                        // waves a block, of 32 query positions each
+constexpr int kThreads = 64 * kNW, kQB = 32 * kNW;
+constexpr int kRing = 2;                      // stages of keys, and of values, in LDS
 
 template <int DH>
 struct Shape {
   static constexpr int kPieces = DH * 2 / 16;            // 16-byte pieces per key row
   static constexpr int kSteps = kPieces / 2;             // S^T MFMA steps per key tile
   static constexpr int kDT = DH / 32;                    // value-dimension tiles of O^T
-  static constexpr int kDma = kKS * kPieces / 64;        // DMA instructions per operand stage
-  static constexpr int kDmaPerWave = kDma / kWaves;      // ... per wave
-  static_assert(kDmaPerWave >= 1 && kDma % kWaves == 0, "stage split");
+  static constexpr int kDma = kKS * kPieces / 64 / kNW;  // DMA instructions per operand stage and wave
+  static constexpr int kPairs = 8 / kSteps;              // probability pairs a chunk (a chunk: one S^T step)
+  static_assert(kKS * kPieces % (64 * kNW) == 0, "stage split");
+  static_assert(kSteps == 2 * kDT && 8 % kSteps == 0, "chunk split");
 };
 
-template <int NP>
-__device__ __forceinline__ int kslot(int j, int p) {
-  return j * NP + (p ^ (NP >= 16 ? (j & 15) : ((j >> 1) & 7)));
-}
-
 // Physical 16-byte piece of logical piece p in row j of a stage (keys and
-// values alike).
+// values alike): an XOR that gives the 16 rows a key fragment reads at one
+// piece 16 different bank groups, and the 4 rows a transpose read takes 64
+// bytes of four different quarters of the banks. (The plain p ^ (j % 16) put
+// those four rows' 64 bytes on the same banks: a third of the time of the
+// long prefill went into the conflicts.)
 template <int NP>
 __device__ __forceinline__ int pswz(int j, int p) {
-  return p ^ (NP >= 16 ? (j & 15) : ((j >> 1) & 7));
+  return p ^ (NP >= 16 ? ((j & 3) << 2) | ((j >> 2) & 3) : ((j & 2) << 1) | ((j >> 2) & 3));
 }
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
@@ -97,7 +109,57 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2_t));
 }
 
-// One (layer, request, head, 128-position block) per block.
+// max over the two halves of the wave (lanes l and l ^ 32), in both
+__device__ __forceinline__ float half_max(float v) {
+  typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+  const u32x2_t r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float half_sum(float v) { return v + __shfl_xor(v, 32); }
+
+// The request's last row against its visual keys (the first of them at kp):
+// its logits again (the same products, bit for bit, with that row in every
+// column and the keys straight from memory, mostly from L2), written in the
+// score pass's base-2 units, and the sum of their terms against the reference
+// mr, of this wave's share. One tile's keys are in flight; with four, the
+// attention loop above it lost its registers to them (64 x 640 tokens: 1003
+// -> 1114 us, and 1070 as a call of its own).
+template <int DH>
+__device__ __forceinline__ float last_row(const uint16_t *qrow, const uint16_t *kp, int64_t kvstride, int nvis,
+                                          float s2, float mr, float *vl, int Hq) {
+  constexpr int kSteps = Shape<DH>::kSteps;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int col = lane & 31, half = lane >> 5;
+  const int tiles = (nvis + 31) / 32;
+  bf16x8_t bq[kSteps], kf[kSteps];
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) bq[s] = *reinterpret_cast<const bf16x8_t *>(qrow + (2 * s + half) * 8);
+  auto load_k = [&](int tile) {
+    const uint16_t *row = kp + min(32 * tile + perm_key(col), nvis - 1) * kvstride;
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) kf[s] = *reinterpret_cast<const bf16x8_t *>(row + (2 * s + half) * 8);
+  };
+  float vsum = 0.f;
+  if (wave < tiles) load_k(wave);
+  for (int tile = wave; tile < tiles; tile += kNW) {
+    f32x16_t sc = f32x16_t{};
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], bq[s], sc, 0, 0, 0);
+    if (tile + kNW < tiles) load_k(tile + kNW);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int i = 32 * tile + acc_key(half, e);
+      const float x2 = sc[e] * s2;
+      if (i < nvis) {
+        vsum += __builtin_amdgcn_exp2f(x2 - mr);
+        if (col == e) vl[(int64_t)i * Hq] = x2;   // every column holds the row: one of them writes
+      }
+    }
+  }
+  return half_sum(vsum);
+}
+
+// One (layer, request, head, block of query positions) per block.
 template <int DH>
 __global__ __launch_bounds__(kThreads, 2) void k_prefill(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
@@ -107,196 +169,259 @@ __global__ __launch_bounds__(kThreads, 2) void k_prefill(
     int64_t T_total, int64_t N_total, float scale, uint16_t *__restrict__ out,
     float *__restrict__ vlog, float4 *__restrict__ stats) {
   using SH = Shape<DH>;
-  __shared__ uint4 s_k[2][kKS * SH::kPieces];
-  __shared__ uint4 s_v[2][kKS * SH::kPieces];
+  constexpr int NP = SH::kPieces;
+  __shared__ uint4 s_kv[2][kRing][kKS * NP];
+  static_assert(kNW * 32 <= 2 * kRing * kKS, "the output rows are staged in the ring");
+  auto &s_k = s_kv[0], &s_v = s_kv[1];
 
-  // The query blocks of one (layer, head, request) are neighbours in this
-  // order; XCD-contiguous numbering runs them together on one XCD, so they
-  // re-read the request's keys and values from its L2 rather than from HBM.
-  int64_t bid = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int64_t qbi = bid % QB_total;
-  bid /= QB_total;
-  const int h = (int)(bid % Hq);
-  const int l = (int)(bid / Hq);
-  const int r = qb_req[qbi];
-  const int qb = (int)(qbi - qb_off[r]);
+  // Order: layer, request, head, query block (the longest, last, block of a
+  // request first). XCD-contiguous numbering runs neighbours together on one
+  // XCD: the query blocks of one head re-read its keys and values from that
+  // L2, and the heads running beside each other cover whole token rows (Hq Dh
+  // elements apart). With every request's blocks of one head before the next
+  // head, all running blocks read the same few 256-byte slots of the rows,
+  // and so the same memory channels: 64 x 640 tokens, 32 heads 1137 us.
+  const int64_t bid = xcd_contiguous(blockIdx.x, gridDim.x), per_layer = (int64_t)Hq * QB_total;
+  const int l = (int)(bid / per_layer);
+  const int64_t in_layer = bid % per_layer;
+  const int r = qb_req[in_layer / Hq];
+  const int in_req = (int)(in_layer - (int64_t)Hq * qb_off[r]), nqb = qb_off[r + 1] - qb_off[r];
+  const int h = in_req / nqb, qb = nqb - 1 - in_req % nqb;
   const int g = Hq / Hkv, kv = h / g;
   const int64_t tok0 = cu_seqlens[r];
   const int P = cu_seqlens[r + 1] - (int)tok0;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, half = lane >> 5;
-  const int q0 = qb * kQB + wave * 32;           // the wave's first query position
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int col = lane & 31, half = lane >> 5;
+  const int q0 = qb * kQB + wave * 32;       // the wave's first query position
   const int qpos = q0 + col;                     // this lane's query
-  const bool qreal = qpos < P;
-  const int kend = min(P, qb * kQB + kQB);       // keys the block needs: 0 .. kend - 1
-  const int wave_last = min(P, q0 + 32) - 1;     // the wave's last real query (-1: none)
+  const int kend = min(P, qb * kQB + kQB);   // keys the block needs: 0 .. kend - 1
+  const int nst = (kend + kKS - 1) / kKS;            // stages of the block, and of the wave
+  const int wst = q0 < P ? (min(P, q0 + 32) - 1) / kKS + 1 : 0;
   const float s2 = scale * kLog2e;
-  const int vlo = vis_start[r], vhi = vlo + (cu_vis[r + 1] - cu_vis[r]);
-  const bool has_last = q0 <= P - 1 && P - 1 < q0 + 32;   // the wave holds the request's last row
 
-  // B operand of S^T: the lane's query row, pieces 2st + half
-  uint4 bq[SH::kSteps];
-  {
-    const char *qp = reinterpret_cast<const char *>(q + (((int64_t)l * T_total + tok0 + min(qpos, P - 1)) * Hq + h) * DH);
+  // B operand of S^T: the lane's query row, pieces 2 st + half
+  bf16x8_t bq[SH::kSteps];
+  auto load_q = [&](int pos) {
+    const char *qp = reinterpret_cast<const char *>(q + (((int64_t)l * T_total + tok0 + pos) * Hq + h) * DH);
 #pragma unroll
-    for (int st = 0; st < SH::kSteps; ++st) bq[st] = *reinterpret_cast<const uint4 *>(qp + (2 * st + half) * 16);
-  }
+    for (int st = 0; st < SH::kSteps; ++st)
+      bq[st] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(qp + (2 * st + half) * 16));
+  };
+  load_q(min(qpos, P - 1));
 
   const int64_t kvstride = (int64_t)Hkv * DH;    // elements between consecutive tokens
   const uint16_t *kbase = k + ((int64_t)l * T_total + tok0) * kvstride + (int64_t)kv * DH;
   const uint16_t *vbase = v + ((int64_t)l * T_total + tok0) * kvstride + (int64_t)kv * DH;
 
-  // One stage: keys j0 .. j0 + 63 (clamped to the block's last needed key) of
-  // both operands. DMA instruction x of this wave covers 16-byte slots
-  // 64 q + lane, q = wave + kWaves x, of the stage: row (slot / kPieces),
-  // physical piece (slot % kPieces), which holds logical piece
-  // pswz(row, physical) (an XOR, its own inverse).
-  auto issue_stage = [&](int j0, int buf) {
+  // One operand stage: rows 64 st .. 64 st + 63 (clamped to the block's last
+  // needed key). DMA instruction x of this wave covers 16-byte slots 64 i +
+  // lane, i = wave + kNW x, of the stage: row (slot / NP), physical piece
+  // (slot % NP), which holds logical piece pswz(row, physical) (an XOR, its
+  // own inverse). The rows of x are 64 kNW / NP x below those of x = 0 and the
+  // piece is the same, so a lane's offset is one register and only the base
+  // moves, but in a last stage that reaches past the keys.
+  constexpr int kRows = 64 * kNW / NP;
+  static_assert(kRows % 16 == 0, "the swizzle repeats every 16 rows");
+  const int drow = (wave * 64 + lane) / NP, dpiece = pswz<NP>(drow, lane % NP) * 16;
+  const uint32_t rowb = (uint32_t)(kvstride * 2), voff0 = drow * rowb + dpiece;
+  auto issue = [&](const uint16_t *base, uint4 *to, int st) {
+    const char *from = reinterpret_cast<const char *>(base) + (int64_t)st * kKS * rowb;
+    if ((st + 1) * kKS <= kend) {
 #pragma unroll
-    for (int x = 0; x < SH::kDmaPerWave; ++x) {
-      const int q = wave + kWaves * x, slot = q * 64 + lane;
-      const int j = slot / SH::kPieces, pp = slot % SH::kPieces;
-      const int jj = min(j0 + j, kend - 1);
-      const uint32_t voff = (uint32_t)(((int64_t)jj * kvstride + pswz<SH::kPieces>(j, pp) * 8) * 2);
-      dma16(__builtin_amdgcn_readfirstlane(lds_u32(&s_k[buf][q * 64])), uniform_ptr(kbase), voff);
-      dma16(__builtin_amdgcn_readfirstlane(lds_u32(&s_v[buf][q * 64])), uniform_ptr(vbase), voff);
+      for (int x = 0; x < SH::kDma; ++x)
+        dma16(__builtin_amdgcn_readfirstlane(lds_u32(to + (wave + kNW * x) * 64)),
+              uniform_ptr(from + (int64_t)(kRows * x) * rowb), voff0);
+    } else {
+#pragma unroll
+      for (int x = 0; x < SH::kDma; ++x)
+        dma16(__builtin_amdgcn_readfirstlane(lds_u32(to + (wave + kNW * x) * 64)), uniform_ptr(from),
+              (uint32_t)min(kRows * x + drow, kend - 1 - st * kKS) * rowb + dpiece);
     }
   };
+  // group g: the keys and values that step g of the loop below reads
+  auto issue_group = [&](int g) {
+    if (g + 1 < nst) issue(kbase, s_k[(g + 1) % kRing], g + 1);
+    if (g < nst) issue(vbase, s_v[g % kRing], g);
+  };
 
-  float m = -INFINITY, lsum = 0.f, vsum = 0.f;   // per lane (= per query), base-2 units
+  // Fragment offsets in an operand stage (elements). Keys: row 32 t +
+  // perm_key(col), piece 2 s + half; the swizzle does not depend on t.
+  // Values (A = V^T): lane l needs dimension 32 dt + l % 32 of keys 16 s + 8
+  // half .. + 7, as two transpose reads of 4 keys; lane i of its 16-lane group
+  // points at key i / 4 of the four and dimensions 4 (i % 4) .. + 3 of the
+  // group's 16; the swizzle does not depend on s.
+  int koff[SH::kSteps], voffs[SH::kDT][2];
+  {
+    const int krow = perm_key(col);
+#pragma unroll
+    for (int s = 0; s < SH::kSteps; ++s) koff[s] = (krow * NP + pswz<NP>(krow, 2 * s + half)) * 8;
+    const int gr = lane >> 4, pl = lane & 15;
+#pragma unroll
+    for (int dt = 0; dt < SH::kDT; ++dt)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int key = 8 * (gr >> 1) + 4 * c + (pl >> 2), d = dt * 32 + 16 * (gr & 1) + 4 * (pl & 3);
+        voffs[dt][c] = key * DH + pswz<NP>(key, d >> 3) * 8 + (d & 7);
+      }
+  }
+  auto kfrag = [&](const uint16_t *ks, int t, int s) {   // key tile t of the stage, step s
+    return *reinterpret_cast<const bf16x8_t *>(ks + koff[s] + t * 32 * DH);
+  };
+  auto vfrag = [&](const uint16_t *vs, int s, int dt) {  // 16-key step s of the stage
+    typedef short s16x8_t __attribute__((ext_vector_type(8)));
+    const s16x4_t a0 = read_tr(vs + voffs[dt][0] + s * 16 * DH), a1 = read_tr(vs + voffs[dt][1] + s * 16 * DH);
+    const s16x8_t av = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
+    return __builtin_bit_cast(bf16x8_t, av);
+  };
+
+  // Per lane (= per query): the reference m of the exponentials (base-2
+  // units) and the sum. The lane's terms cover its half's keys; the halves are
+  // added at the end.
+  float m = -INFINITY, lsum = 0.f;
   f32x16_t o[SH::kDT];
 #pragma unroll
   for (int dt = 0; dt < SH::kDT; ++dt) o[dt] = f32x16_t{};
 
-  const int nst = (kend + kKS - 1) / kKS;
-  issue_stage(0, 0);
-  vm_wait<0>();
-  __syncthreads();
-  for (int st = 0; st < nst; ++st) {
-    // the other buffer was last read in stage st - 1, which every wave has left
-    if (st + 1 < nst) issue_stage((st + 1) * kKS, (st + 1) & 1);
-    const int k0 = st * kKS;
-    if (k0 <= wave_last) {
-      const uint4 *kb = s_k[st & 1];
-      const uint16_t *vs = reinterpret_cast<const uint16_t *>(s_v[st & 1]);
-      // The fragment addresses derive from the lane index anew in every stage
-      // (opaque to the compiler), instead of two dozen of them being hoisted
-      // out of the loop and held in registers.
-      int ln = (int)threadIdx.x & 63;
-      asm volatile("" : "+v"(ln));
-      const int lcol = ln & 31, lhalf = ln >> 5;
-      // S^T for the stage's two 32-key tiles
-      f32x16_t sc[2];
+  // keys a query does not see (causal mask, past the block's end) are -inf
+  auto mask = [&](f32x16_t &sc, int u) {
+    if (32 * u + 31 <= q0) return;   // every query of the wave sees every key
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        sc[t] = f32x16_t{};
-        const int krow = t * 32 + perm_key(lcol);
-#pragma unroll
-        for (int s = 0; s < SH::kSteps; ++s)
-          sc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              __builtin_bit_cast(bf16x8_t, kb[kslot<SH::kPieces>(krow, 2 * s + lhalf)]),
-              __builtin_bit_cast(bf16x8_t, bq[s]), sc[t], 0, 0, 0);
-      }
-      // base-2 logits: the raw dots stay in place and the scale goes into the
-      // exponent (s2 > 0, so the largest dot gives the largest logit); keys a
-      // query does not see (causal mask, past the block's end) are -inf
-      const bool full = k0 + kKS - 1 <= q0;   // every query of the wave sees every key
-      if (!full) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int key = k0 + t * 32 + acc_key(half, e);
-            sc[t][e] = (key <= qpos && key < kend) ? sc[t][e] : -INFINITY;
-          }
-      }
-      float mx = sc[0][0];
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sc[t][e]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32)) * s2;
-      const float mnew = fmaxf(m, mx);
-      // a query with no key seen yet keeps -inf; its terms are 0 and its
-      // factor 1 (its sums are still 0)
-      const float mref = mnew == -INFINITY ? 0.f : mnew;
-      const float alpha = __builtin_amdgcn_exp2f(m - mref);
-      float ps = 0.f, pv = 0.f;
-      uint32_t pb[2][8];
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int e = 0; e < 16; e += 2) {
-          const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[t][e], s2, -mref));
-          const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[t][e + 1], s2, -mref));
-          ps += p0 + p1;
-          if (has_last) {
-            const int key = k0 + t * 32 + acc_key(half, e);
-            pv += (key >= vlo && key < vhi ? p0 : 0.f) + (key + 1 >= vlo && key + 1 < vhi ? p1 : 0.f);
-          }
-          pb[t][e / 2] = pack_bf16(p0, p1);
-        }
-      ps += __shfl_xor(ps, 32);
-      lsum = lsum * alpha + ps;
-      if (has_last) {
-        pv += __shfl_xor(pv, 32);
-        vsum = vsum * alpha + pv;
-      }
-      // the running max moves rarely after the first stages: rescale only then
-      if (__any(mnew != m)) {
-#pragma unroll
-        for (int dt = 0; dt < SH::kDT; ++dt) o[dt] *= alpha;
-      }
-      m = mnew;
-      // O^T += V^T P^T: four 16-key steps, each lane's B operand being 8 of
-      // its own probabilities (keys 16s + 8 half .. + 7 of the stage)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const uint32_t *pw = &pb[s >> 1][(s & 1) * 4];
-        const uint4 bp = make_uint4(pw[0], pw[1], pw[2], pw[3]);
-#pragma unroll
-        for (int dt = 0; dt < SH::kDT; ++dt) {
-          // A = V^T: lane l needs dimension dt 32 + l % 32 of keys 16 s + 8 half
-          // .. + 7, as two transpose reads of 4 keys; lane p of its 16-lane
-          // group points at key (p / 4) of the four and dimensions
-          // 4 (p % 4) .. + 3 of the group's 16
-          const int g = ln >> 4, pl = ln & 15;
-          const int d = dt * 32 + 16 * (g & 1) + 4 * (pl & 3);   // first dimension of the chunk
-          s16x4_t tv[2];
-#pragma unroll
-          for (int c = 0; c < 2; ++c) {
-            const int key = 16 * s + 8 * (g >> 1) + 4 * c + (pl >> 2);
-            tv[c] = read_tr(vs + key * DH + pswz<SH::kPieces>(key, d >> 3) * 8 + (d & 7));
-          }
-          const s16x4_t a0 = tv[0], a1 = tv[1];
-          typedef short s16x8_t __attribute__((ext_vector_type(8)));
-          const s16x8_t av = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
-          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, av),
-                                                          __builtin_bit_cast(bf16x8_t, bp), o[dt], 0, 0, 0);
-        }
-      }
-      // the request's last row: its visual logits, in the score pass's base-2
-      // units
-      if (has_last && qpos == P - 1) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int key = k0 + t * 32 + acc_key(half, e);
-            if (key >= vlo && key < vhi && key < kend)
-              vlog[((int64_t)l * N_total + cu_vis[r] + key - vlo) * Hq + h] = sc[t][e] * s2;
-          }
-      }
+    for (int e = 0; e < 16; ++e) {
+      const int key = 32 * u + acc_key(half, e);
+      sc[e] = (key <= qpos && key < kend) ? sc[e] : -INFINITY;
     }
-    // the next stage has landed (this wave's copies), and every wave's after
-    // the barrier
+  };
+  // Probabilities of elements 2 i and 2 i + 1, packed: the raw dots stay in
+  // place and the scale goes into the exponent.
+  auto pair = [&](const f32x16_t &sc, uint32_t (&pb)[8], float &ps, float mr, int i) {
+    const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[2 * i], s2, -mr));
+    const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[2 * i + 1], s2, -mr));
+    ps += p0 + p1;
+    pb[i] = pack_bf16(p0, p1);
+  };
+  auto ref = [](float x) { return x == -INFINITY ? 0.f : x; };
+  // What remains of a unit's softmax once its terms are there. If they passed
+  // kMoveAt (or are not numbers, or it is the first unit), move the reference
+  // to the largest logit, rescale what was summed against the old one and form
+  // the terms again. (s2 > 0, so the largest dot gives the largest logit. A
+  // query with no key seen yet keeps -inf; its terms and sums are 0.)
+  auto close = [&](const f32x16_t &sc, uint32_t (&pb)[8], float &ps, bool first) {
+    if (first || __any(!(ps < kMoveAt))) {
+      float mx = sc[0];
+#pragma unroll
+      for (int e = 1; e < 16; ++e) mx = fmaxf(mx, sc[e]);
+      const float mnew = fmaxf(m, half_max(mx) * s2), mr = ref(mnew);
+      const float alpha = __builtin_amdgcn_exp2f(m - mr);
+      m = mnew;
+      lsum *= alpha;
+      ps = 0.f;
+#pragma unroll
+      for (int dt = 0; dt < SH::kDT; ++dt) o[dt] *= alpha;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) pair(sc, pb, ps, mr, i);
+    }
+    lsum += ps;
+  };
+  auto bfrag = [&](const uint32_t (&pb)[8], int s) {
+    return __builtin_bit_cast(bf16x8_t, make_uint4(pb[4 * s], pb[4 * s + 1], pb[4 * s + 2], pb[4 * s + 3]));
+  };
+
+  // The loop is pipelined by units of 32 keys: while the vector ALU forms
+  // unit u's probabilities, the matrix cores form unit u + 1's logits and add
+  // unit u - 1's probabilities times the values. Step j takes units 2 j + 1
+  // and 2 j + 2, which read the keys of stage j + 1 and the values of stage j.
+  issue(kbase, s_k[0], 0);
+  issue_group(0);
+  if (nst > 1)
+    vm_wait<2 * SH::kDma>();
+  else
+    vm_wait<0>();
+  __syncthreads();
+  f32x16_t sa, sb;
+  uint32_t pa[8], pn[8];
+  if (wst > 0) {
+    const uint16_t *ks = reinterpret_cast<const uint16_t *>(s_k[0]);
+    sa = sb = f32x16_t{};
+#pragma unroll
+    for (int s = 0; s < SH::kSteps; ++s) {
+      sb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag(ks, 0, s), bq[s], sb, 0, 0, 0);
+      sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag(ks, 1, s), bq[s], sa, 0, 0, 0);
+    }
+    mask(sb, 0);
+    float ps = 0.f;
+    close(sb, pa, ps, true);
+    mask(sa, 1);
+  }
+  // One unit: softmax of `cur` into pnew, the logits of the next unit into
+  // `next` (key tile t of ks), and the values of 16-key steps 2 t, 2 t + 1 of
+  // vs times pold. A chunk is a key and a value fragment from LDS (read two
+  // chunks ahead), an MFMA of each product and a share of the probabilities.
+  auto unit = [&](auto logits, f32x16_t &cur, f32x16_t &next, const uint32_t (&pold)[8], uint32_t (&pnew)[8],
+                  const uint16_t *ks, const uint16_t *vs, int t) {
+    constexpr bool LOGITS = decltype(logits)::value;
+    bf16x8_t kf[3], vf[3];
+    const float mr = ref(m);
+    float ps = 0.f;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      if (LOGITS) kf[i] = kfrag(ks, t, i);
+      vf[i] = vfrag(vs, 2 * t + i / SH::kDT, i % SH::kDT);
+    }
+#pragma unroll
+    for (int c = 0; c < SH::kSteps; ++c) {
+      if (c + 2 < SH::kSteps) {
+        if (LOGITS) kf[(c + 2) % 3] = kfrag(ks, t, c + 2);
+        vf[(c + 2) % 3] = vfrag(vs, 2 * t + (c + 2) / SH::kDT, (c + 2) % SH::kDT);
+      }
+      if (LOGITS)
+        next = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[c % 3], bq[c], c == 0 ? f32x16_t{} : next, 0, 0, 0);
+      o[c % SH::kDT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[c % 3], bfrag(pold, c / SH::kDT), o[c % SH::kDT],
+                                                               0, 0, 0);
+#pragma unroll
+      for (int x = 0; x < SH::kPairs; ++x) pair(cur, pnew, ps, mr, c * SH::kPairs + x);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    close(cur, pnew, ps, false);
+  };
+  // (steps in pairs, so that the ring slots, and with them every fragment's
+  // address but the lane's part, are constants)
+  static_assert(kRing == 2, "slot parity");
+  auto step = [&](auto parity, int j) {
+    constexpr int kSlot = decltype(parity)::value;   // j % 2
+    // group j has landed for this wave; the barrier publishes it and retires
+    // every read of the slots group j + 1 overwrites
     vm_wait<0>();
     __syncthreads();
+    issue_group(j + 1);
+    const uint16_t *ks = reinterpret_cast<const uint16_t *>(s_kv[0][1 - kSlot]);
+    const uint16_t *vs = reinterpret_cast<const uint16_t *>(s_kv[1][kSlot]);
+    if (j + 1 < wst) {
+      unit(std::true_type{}, sa, sb, pa, pn, ks, vs, 0);
+      mask(sb, 2 * j + 2);
+      unit(std::true_type{}, sb, sa, pn, pa, ks, vs, 1);
+      mask(sa, 2 * j + 3);
+    } else if (j + 1 == wst) {
+      unit(std::false_type{}, sa, sb, pa, pn, ks, vs, 0);
+#pragma unroll
+      for (int c = 0; c < SH::kSteps; ++c)
+        o[c % SH::kDT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfrag(vs, 2 + c / SH::kDT, c % SH::kDT),
+                                                                 bfrag(pn, c / SH::kDT), o[c % SH::kDT], 0, 0, 0);
+    }
+  };
+  for (int j = 0; j < nst; j += 2) {
+    step(std::integral_constant<int, 0>{}, j);
+    if (j + 1 < nst) step(std::integral_constant<int, 1>{}, j + 1);
   }
 
-  // out_p = O^T column / sum; lane half h holds dimensions 4h + e % 4 + 8 (e / 4)
-  if (qreal) {
-    const float inv = 1.0f / lsum;
-    uint16_t *op = out + (((int64_t)l * T_total + tok0 + qpos) * Hq + h) * DH;
+  // out_p = O^T column / sum; lane half h holds dimensions 4 h + e % 4 + 8 (e /
+  // 4) of its query. The wave's 32 rows go through LDS (free once every wave
+  // is past its last read; rows of NP 16-byte pieces, swizzled like a stage)
+  // and leave as whole rows.
+  __syncthreads();
+  const float lall = half_sum(lsum);
+  if (wst > 0) {
+    uint4 *rows = &s_kv[0][0][0] + wave * 32 * NP;
+    const float inv = 1.0f / lall;
 #pragma unroll
     for (int dt = 0; dt < SH::kDT; ++dt)
 #pragma unroll
@@ -305,12 +430,39 @@ __global__ __launch_bounds__(kThreads, 2) void k_prefill(
         uint2 w;
         w.x = pack_bf16(o[dt][e] * inv, o[dt][e + 1] * inv);
         w.y = pack_bf16(o[dt][e + 2] * inv, o[dt][e + 3] * inv);
-        *reinterpret_cast<uint2 *>(op + d) = w;
+        reinterpret_cast<uint2 *>(rows + col * NP + pswz<NP>(col, d >> 3))[half] = w;
       }
+    // (the wave's own rows: its LDS operations complete in order)
+    uint16_t *ob = out + (((int64_t)l * T_total + tok0 + q0) * Hq + h) * DH;
+#pragma unroll 4
+    for (int x = 0; x < NP / 2; ++x) {
+      const int slot = x * 64 + lane, row = slot / NP, pp = slot % NP;
+      const uint4 w = rows[row * NP + pswz<NP>(row, pp)];
+      if (q0 + row < P) *reinterpret_cast<uint4 *>(ob + (int64_t)row * Hq * DH + pp * 8) = w;
+    }
   }
-  // the last row's statistics as one chunk of the score pass: (max, sum, visual sum)
-  if (has_last && qpos == P - 1 && half == 0)
-    stats[((int64_t)l * Hq + h) * R + r] = make_float4(m, lsum, vsum, 0.f);
+
+  // The LAST extraction, by the block that holds the request's last row.
+  if (kend != P) return;
+  __shared__ float s_last[2], s_vsum[kNW];
+  if (q0 <= P - 1 && P - 1 < q0 + 32 && qpos == P - 1 && half == 0) {
+    s_last[0] = m;
+    s_last[1] = lall;
+  }
+  __syncthreads();
+  const float mlast = s_last[0];
+  const float vsum =
+      last_row<DH>(q + (((int64_t)l * T_total + tok0 + P - 1) * Hq + h) * DH, kbase + vis_start[r] * kvstride, kvstride,
+                   cu_vis[r + 1] - cu_vis[r], s2, mlast == -INFINITY ? 0.f : mlast,
+                   vlog + ((int64_t)l * N_total + cu_vis[r]) * Hq + h, Hq);
+  if (lane == 0) s_vsum[wave] = vsum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float vs = 0.f;
+#pragma unroll
+    for (int w = 0; w < kNW; ++w) vs += s_vsum[w];
+    stats[((int64_t)l * Hq + h) * R + r] = make_float4(mlast, s_last[1], vs, 0.f);
+  }
 }
 
 // Per request: the number of 128-position query blocks, their prefix and the
@@ -336,6 +488,19 @@ __global__ __launch_bounds__(256) void k_prefill_plan(const int32_t *__restrict_
   if (threadIdx.x == 0) qb_off[R] = carry;
 }
 
+template <int DH>
+hipError_t launch_dh(const last_batch *b, int64_t QB_total, const int32_t *qb_off, const int32_t *qb_req,
+                        const void *q, const void *k, const void *v, void *out, float *vlog, float4 *stats,
+                        float scale, hipStream_t s) {
+  const int64_t blocks = (int64_t)b->G * b->Hq * QB_total;
+  const int64_t T_total = b->cu_seqlens_h[b->R], N_total = b->cu_vis_h[b->R];
+  last::launch_begin("prefill", s);
+  hipLaunchKernelGGL(k_prefill<DH>, dim3((unsigned)blocks), dim3(kThreads), 0, s, (const uint16_t *)q,
+                     (const uint16_t *)k, (const uint16_t *)v, b->cu_seqlens, b->vis_start, b->cu_vis, qb_off,
+                     qb_req, b->R, b->Hq, b->Hkv, QB_total, T_total, N_total, scale, (uint16_t *)out, vlog, stats);
+  return last::launch_end(s);
+}
+
 }  // namespace
 
 namespace last {
@@ -353,20 +518,8 @@ hipError_t launch_prefill(const last_batch *b, int64_t QB_total, int32_t *qb_off
   hipLaunchKernelGGL(k_prefill_plan, dim3(1), dim3(256), 0, s, b->cu_seqlens, b->R, QB_total, qb_off, qb_req);
   hipError_t e = launch_end(s);
   if (e != hipSuccess) return e;
-  const int64_t blocks = (int64_t)b->G * b->Hq * QB_total;
-  const int64_t T_total = b->cu_seqlens_h[b->R], N_total = b->cu_vis_h[b->R];
-  launch_begin("prefill", s);
-  if (b->Dh == 64)
-    hipLaunchKernelGGL(k_prefill<64>, dim3((unsigned)blocks), dim3(kThreads), 0, s, (const uint16_t *)q,
-                       (const uint16_t *)k, (const uint16_t *)v, b->cu_seqlens, b->vis_start, b->cu_vis,
-                       qb_off, qb_req, b->R, b->Hq, b->Hkv, QB_total, T_total, N_total, scale,
-                       (uint16_t *)out, vlog, stats);
-  else
-    hipLaunchKernelGGL(k_prefill<128>, dim3((unsigned)blocks), dim3(kThreads), 0, s, (const uint16_t *)q,
-                       (const uint16_t *)k, (const uint16_t *)v, b->cu_seqlens, b->vis_start, b->cu_vis,
-                       qb_off, qb_req, b->R, b->Hq, b->Hkv, QB_total, T_total, N_total, scale,
-                       (uint16_t *)out, vlog, stats);
-  return launch_end(s);
+  return b->Dh == 64 ? launch_dh<64>(b, QB_total, qb_off, qb_req, q, k, v, out, vlog, stats, scale, s)
+                     : launch_dh<128>(b, QB_total, qb_off, qb_req, q, k, v, out, vlog, stats, scale, s);
 }
 
 }  // namespace last

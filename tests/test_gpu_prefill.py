@@ -170,3 +170,72 @@ def test_config_prefill(name):
         expect = orc_prefill(grp, pg)
         got = bf16_to_f64(out[:, a:a + n, hs].contiguous())
         assert_out(grp, pg.v, got, expect, f"{name} request {r} heads {hs}")
+
+
+def _f64_prefill(q, k, v, cu, scale):
+    """Causal softmax attention in fp64 (out, and the last position's probabilities
+    of each request: [Hq][P_r])."""
+    G, T, Hq, Dh = q.shape
+    g = Hq // k.shape[2]
+    out, rows = torch.empty(q.shape, dtype=torch.float64, device=q.device), []
+    for a, b in zip(cu[:-1], cu[1:]):
+        acc = []
+        for h in range(Hq):
+            z = q[0, a:b, h].double() @ k[0, a:b, h // g].double().t() * scale
+            z = z.masked_fill(torch.ones_like(z, dtype=torch.bool).triu(1), -torch.inf)
+            p = torch.softmax(z, -1)
+            out[0, a:b, h] = p @ v[0, a:b, h // g].double()
+            acc.append(p[-1])
+        rows.append(torch.stack(acc))
+    return out, rows
+
+
+@pytest.mark.parametrize("Dh", [64, 128])
+@pytest.mark.parametrize("kind", ["rising", "spikes", "low"])
+def test_prefill_moving_reference(Dh, kind):
+    """Logits that leave the reference of the first keys behind: rising by
+    hundreds of powers of two along the sequence, single keys far above the
+    rest, and all far below zero. Lengths around the 32-key units, the 64-key
+    stages and the 128-query blocks. The bar is the module's: 2^-8 V for the
+    rounded probabilities, 2^-8 of the output and the fp32 sums, with V = max
+    |v| over the row's keys."""
+    P = [2, 31, 33, 64, 65, 127, 128, 129, 192, 257, 300]
+    cu = np.concatenate([[0], np.cumsum(P)]).astype(np.int32)
+    T, Hq, Hkv = int(cu[-1]), 4, 2
+    gen = torch.Generator("cuda").manual_seed(Dh)
+    rnd = lambda *s: torch.randn(s, device="cuda", generator=gen)
+    q, k, v = rnd(1, T, Hq, Dh), rnd(1, T, Hkv, Dh), rnd(1, T, Hkv, Dh).bfloat16()
+    q[..., 0], k[..., 0] = 8.0, 0.0
+    pos = torch.cat([torch.arange(n, device="cuda") for n in P])
+    if kind == "rising":
+        k[0, :, :, 0] = (pos * 2.0)[:, None]
+    elif kind == "spikes":
+        k[0, pos % 37 == 36, :, 0] = 300.0
+        k[0, pos % 101 == 100, :, 0] = 900.0
+    else:
+        k[..., 0] = -600.0
+    q, k = q.bfloat16(), k.bfloat16()
+    vis = np.array([max(1, n - 1 - n // 3) for n in P])
+    start = np.array([(n - 1 - m) // 2 for n, m in zip(P, vis)], np.int32)
+    b = last.Batch.make(1, Hq, Hkv, Dh, cu, start, np.concatenate([[0], np.cumsum(vis)]).astype(np.int32))
+    out, scores = last.prefill_attention(b, q, k, v)
+    ref, rows = _f64_prefill(q, k, v, cu, 1 / np.sqrt(Dh))
+    V = torch.cat([v[0, x:y].double().abs().amax(-1).cummax(0).values for x, y in zip(cu[:-1], cu[1:])])  # [T][Hkv]
+    V = V.repeat_interleave(Hq // Hkv, 1)[None, :, :, None]
+    n = (pos + 1)[None, :, None, None]
+    bound = 2.0 ** -8 * (V + ref.abs()) + 2.0 ** -22 * n * V + 1e-5 * V
+    bad = (out.double() - ref).abs() > bound
+    assert not bad.any(), f"{int(bad.sum())} outputs off"
+    a = 0
+    for r, p in enumerate(rows):
+        s = p[:, start[r]:start[r] + vis[r]].sum(0)
+        want = s / s.sum()
+        got = scores[a:a + vis[r]].double()
+        a += int(vis[r])
+        if not float(s.sum()) > 2.0 ** -100:   # Eq. 8's sum leaves fp32: no score to compare
+            continue
+        # fp32 logits of size x carry an error of x 2^-22 into the exponent; a
+        # head's probability below 2^-126 counts as 0, before the division by s.sum()
+        tol = 1e-5 + 8.0 * 900.0 / np.sqrt(Dh) * 2.0 ** -22 * 8
+        floor = Hq * 2.0 ** -125 / float(s.sum())
+        assert torch.all((got - want).abs() <= tol * want + floor), f"request {r}"
