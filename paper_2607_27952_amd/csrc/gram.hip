@@ -19,9 +19,11 @@
 //                   yields |x_i|^2 from the same arithmetic (so a row and its
 //                   bitwise duplicate get distance exactly 0); a second launch
 //                   covers the tiles above the diagonal and mirrors them.
-//   k_gram_f32      the same for fp32 features, in fp64 VALU FMAs over
-//                   32 x 32 sub-tiles; the diagonal sub-tiles run first and
-//                   yield the norms from the same FMA chains.
+//   k_gram_pairs    the same numbers for a small batch, one 32 x 32 sub-tile a
+//                   block, all in one launch.
+//   k_gram_f32      the same for fp32 features, in fp64 on the matrix cores
+//                   over 32 x 32 sub-tiles, with the norms from the same FMA
+//                   chains.
 #include <algorithm>
 #include <atomic>
 #include <math.h>
@@ -939,31 +941,29 @@ __global__ __launch_bounds__(kGramThreads) void k_gram_bf16(
   }
 }
 
-// fp32 features: every dot product, squared norms included, is one fp64 FMA
-// chain over d = 0..Dv-1 in order, so a row and its bitwise duplicate get
-// distance exactly 0. One launch covers every 32 x 32 sub-tile that a
-// request's coverage matrix needs: blocks [0, 16 tiles_diag) take sub-tile
-// b % 16 of diagonal tile b / 16 (those below its diagonal return at once),
-// the rest the sub-tiles of the off-diagonal tiles. 2 x 2 outputs a thread,
-// over 64-column chunks staged through LDS, with four chunks of loads in
-// flight. Wave 0 also runs the squared-norm chains of the block's 32 A rows
-// and 32 B rows, the same FMAs in the same order as a dot product of a row
-// with itself, so no block waits for another's norms. Sub-tiles on a
-// diagonal write the norms out; those above it, and every off-diagonal
-// sub-tile, also write the mirror.
-constexpr int kF32Sub = 32, kF32KS = 64, kF32Subs = (kTile / kF32Sub) * (kTile / kF32Sub);
-constexpr int kF32Per = kF32Sub * kF32KS / 256;   // staged elements per thread and operand
-constexpr int kF32Ahead = 4;                      // chunks of loads in flight
+// A small batch of bf16 features: one 32 x 32 sub-tile a block, every
+// sub-tile at once. The 128 x 128 tiles of one request of 576 tokens are 5 + 10
+// blocks in two dependent launches, each a serial walk over 64-column stages;
+// its 171 sub-tiles fill the chip. The eight waves take the 128-column chunks
+// in turn, straight from memory into the matrix cores' layout, and keep each
+// chunk's fp32 partial sums in LDS; the chunks are then added in column order
+// in fp64, as k_gram_bf16 folds them, so every distance is the same number.
+// The squared norms of the block's own rows come from the same chunks (the
+// diagonals of A A^T and B B^T), so no block waits for another's.
+// Bound by the latency of a block's 64 rows (512 KB at Dv = 4096 through one
+// compute unit). 576 tokens x 4096, one request: 60 -> 22 us.
+constexpr int kPairWaves = 8, kPairThreads = 64 * kPairWaves, kPairMaxChunks = 32;   // Dv <= 4096
+constexpr int kSub = 32, kSubs = (kTile / kSub) * (kTile / kSub);   // sub-tiles of a tile
 
-__global__ __launch_bounds__(256) void k_gram_f32(
-    const float *__restrict__ X, const TileMeta *__restrict__ dmeta, const TileMeta *__restrict__ ometa,
+__global__ __launch_bounds__(kPairThreads) void k_gram_pairs(
+    const uint16_t *__restrict__ X, const TileMeta *__restrict__ dmeta, const TileMeta *__restrict__ ometa,
     double *__restrict__ nn, double *__restrict__ inv, int Dv, int64_t tiles_diag, int64_t tiles_off,
     int64_t d_cap, float *__restrict__ dmat) {
-  __shared__ float sA[kF32KS][kF32Sub + 1];
-  __shared__ float sB[kF32KS][kF32Sub + 1];
-  __shared__ double s_nn[2][kF32Sub], s_inv[2][kF32Sub];   // [0]: A rows, [1]: B rows
-  const int64_t t_glob = blockIdx.x / kF32Subs;
-  const int sub = blockIdx.x % kF32Subs, sa = sub / (kTile / kF32Sub), sb = sub % (kTile / kF32Sub);
+  __shared__ float part[kPairMaxChunks][1024];
+  __shared__ float npart[2][kPairMaxChunks][kSub];
+  __shared__ double s_nn[2][kSub], s_inv[2][kSub];   // [0]: A rows, [1]: B rows
+  const int64_t t_glob = blockIdx.x / kSubs;
+  const int sub = blockIdx.x % kSubs, sa = sub / (kTile / kSub), sb = sub % (kTile / kSub);
   const bool on_diag = t_glob < tiles_diag;
   if (t_glob >= tiles_diag + tiles_off) return;
   if (on_diag && sb < sa) return;
@@ -971,90 +971,246 @@ __global__ __launch_bounds__(256) void k_gram_f32(
   const TileMeta m = on_diag ? dmeta[t_glob] : ometa[t_glob - tiles_diag];
   const int64_t n0 = m.n0;
   const int N = m.n, I = m.ij >> 16, J = m.ij & 0xFFFF;
-  const int rowA0 = I * kTile + sa * kF32Sub, rowB0 = J * kTile + sb * kF32Sub;
+  const int rowA0 = I * kTile + sa * kSub, rowB0 = J * kTile + sb * kSub;
+  if (rowA0 >= N || rowB0 >= N) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nc = Dv / 128;
+  const uint16_t *pa = X + (n0 + min(rowA0 + (lane & 31), N - 1)) * (int64_t)Dv + 8 * (lane >> 5);
+  const uint16_t *pb = X + (n0 + min(rowB0 + (lane & 31), N - 1)) * (int64_t)Dv + 8 * (lane >> 5);
+  // this lane's diagonal element, if any: column c = lane % 32 sits in half
+  // (c % 8) / 4 at accumulator element 4 (c / 8) + c % 4
+  const int c = lane & 31;
+  const bool has = ((c & 7) >> 2) == (lane >> 5);
+  const int vsel = 4 * (c >> 3) + (c & 3);
+  auto load = [&](int ch, uint4 (&fa)[8], uint4 (&fb)[8]) {
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      fa[s] = *reinterpret_cast<const uint4 *>(pa + ch * 128 + 16 * s);
+      if (!self) fb[s] = *reinterpret_cast<const uint4 *>(pb + ch * 128 + 16 * s);
+    }
+  };
+  auto product = [&](const uint4 (&x)[8], const uint4 (&y)[8]) {
+    f32x16 acc = f32x16{};
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x[s]), __builtin_bit_cast(bf16x8, y[s]),
+                                                    acc, 0, 0, 0);
+    return acc;
+  };
+  auto diagonal = [&](const f32x16 &acc, int side, int ch) {
+    float x = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) x = v == vsel ? acc[v] : x;
+    if (has) npart[side][ch][c] = x;
+  };
+  auto chunk = [&](int ch, const uint4 (&fa)[8], const uint4 (&fb)[8]) {
+    const f32x16 aa = product(fa, fa);
+    diagonal(aa, 0, ch);
+    if (self) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) part[ch][v * 64 + lane] = aa[v];
+      return;
+    }
+    diagonal(product(fb, fb), 1, ch);
+    const f32x16 ab = product(fa, fb);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) part[ch][v * 64 + lane] = ab[v];
+  };
+  // chunks wave, wave + 8, ... in two register sets, one chunk ahead
+  uint4 xa[8], xb[8], ya[8], yb[8];
+  if (wave < nc) load(wave, xa, xb);
+  for (int ch = wave; ch < nc; ch += 2 * kPairWaves) {
+    const int c1 = ch + kPairWaves, c2 = ch + 2 * kPairWaves;
+    if (c1 < nc) load(c1, ya, yb);
+    chunk(ch, xa, xb);
+    if (c2 < nc) load(c2, xa, xb);
+    if (c1 < nc) chunk(c1, ya, yb);
+  }
+  __syncthreads();
+  if (tid < 2 * kSub) {
+    const int side = tid >> 5, r = tid & 31;
+    double v = 0.0;
+    for (int ch = 0; ch < nc; ++ch) v += (double)npart[self ? 0 : side][ch][r];
+    s_nn[side][r] = v;
+    s_inv[side][r] = v > 0.0 ? 1.0 / sqrt(v) : 0.0;
+    if (self && side == 0 && rowA0 + r < N) {
+      nn[n0 + rowA0 + r] = v;
+      inv[n0 + rowA0 + r] = s_inv[0][r];
+    }
+  }
+  __syncthreads();
+  const int64_t nbr = cov_blocks(N);
+  if (m.doff + nbr * nbr * kCovTileElems > d_cap) return;
+  float *DA = dmat + m.doff + ((int64_t)I * nbr + J) * kCovTileElems;
+  float *DB = dmat + m.doff + ((int64_t)J * nbr + I) * kCovTileElems;
+#pragma unroll
+  for (int h = 0; h < 1024 / kPairThreads; ++h) {
+    const int e = tid + h * kPairThreads, v = e >> 6, l = e & 63;
+    const int i = (l >> 5) * 4 + (v & 3) + 8 * (v >> 2), j = l & 31;   // A row, B column
+    double dot = 0.0;
+    for (int ch = 0; ch < nc; ++ch) dot += (double)part[ch][e];
+    if (rowA0 + i >= N || rowB0 + j >= N) continue;
+    const float d = self && i == j ? kSelfMark : coverage(dot, s_nn[0][i], s_nn[1][j], s_inv[0][i], s_inv[1][j]);
+    DA[(sa * kSub + i) * kTile + sb * kSub + j] = d;
+    if (!self) DB[(sb * kSub + j) * kTile + sa * kSub + i] = d;
+  }
+}
+
+// fp32 features: every dot product, squared norms included, is one fp64 FMA
+// chain over d = 0..Dv-1 in order, so a row and its bitwise duplicate get
+// distance exactly 0. v_mfma_f64_16x16x4_f64 is that chain: it adds its four
+// products to the accumulator one after another (measured: bit-equal to fma in
+// ascending order). One launch covers every 32 x 32 sub-tile that a request's
+// coverage matrix needs: blocks [0, 16 tiles_diag) take sub-tile b % 16 of
+// diagonal tile b / 16 (those below its diagonal return at once), the rest the
+// sub-tiles of the off-diagonal tiles. Each of four waves holds a 16 x 16
+// quadrant, over 64-column chunks staged through LDS (two buffers, one barrier
+// a chunk), with four chunks of loads in flight. The squared norms of the
+// block's 32 A and 32 B rows are the diagonals of four more 16 x 16 products,
+// one a wave, of an operand it holds anyway, so no block waits for another's
+// norms. (A fifth wave running them as vector FMAs waits behind the matrix
+// instructions for the fp64 unit: 32 us where this takes 31.) Sub-tiles on a
+// diagonal write the norms out; those above it, and every off-diagonal
+// sub-tile, also write the mirror.
+// Bound by the fp64 matrix rate (64 cycles a 16 x 16 x 4 step, Dv / 4 steps in
+// a chain, two chains a wave). 576 tokens x 1024: 83 us with vector FMAs,
+// 34 with the loads and stores between the chunks' products, 31 among them.
+constexpr int kF32KS = 64;
+constexpr int kF32Threads = 256;
+constexpr int kF32Per = kSub * kF32KS / kF32Threads;   // staged elements per thread and operand
+constexpr int kF32Ahead = 4;                           // chunks of loads in flight
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+__global__ __launch_bounds__(kF32Threads) void k_gram_f32(
+    const float *__restrict__ X, const TileMeta *__restrict__ dmeta, const TileMeta *__restrict__ ometa,
+    double *__restrict__ nn, double *__restrict__ inv, int Dv, int64_t tiles_diag, int64_t tiles_off,
+    int64_t d_cap, float *__restrict__ dmat) {
+  __shared__ float sA[2][kF32KS][kSub + 1];
+  __shared__ float sB[2][kF32KS][kSub + 1];
+  __shared__ double s_nn[2][kSub], s_inv[2][kSub];   // [0]: A rows, [1]: B rows
+  const int64_t t_glob = blockIdx.x / kSubs;
+  const int sub = blockIdx.x % kSubs, sa = sub / (kTile / kSub), sb = sub % (kTile / kSub);
+  const bool on_diag = t_glob < tiles_diag;
+  if (t_glob >= tiles_diag + tiles_off) return;
+  if (on_diag && sb < sa) return;
+  const bool self = on_diag && sb == sa;
+  const TileMeta m = on_diag ? dmeta[t_glob] : ometa[t_glob - tiles_diag];
+  const int64_t n0 = m.n0;
+  const int N = m.n, I = m.ij >> 16, J = m.ij & 0xFFFF;
+  const int rowA0 = I * kTile + sa * kSub, rowB0 = J * kTile + sb * kSub;
   if (rowA0 >= N || rowB0 >= N) return;
   float *D = dmat + m.doff;
   const int64_t nbr = cov_blocks(N), dlim = d_cap - m.doff;
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  // A block has one wave per SIMD, so a chunk's loads cannot hide behind
-  // other waves: kF32Ahead chunks are in flight in a register ring while the
-  // current one is multiplied.
+  // Few waves a block, so nothing hides behind other waves: kF32Ahead chunks
+  // of loads are in flight in a register ring, and each chunk's stores to LDS
+  // and new loads go out among the matrix instructions of the chunk before it.
+  // Columns past Dv are 0 (a product of 0 leaves the chain as it is); rows past
+  // N repeat the last one (their distances are not stored).
   float pa[kF32Ahead][kF32Per], pb[kF32Ahead][kF32Per];
-  auto fetch = [&](int k0, float (&fa)[kF32Per], float (&fb)[kF32Per]) {
-#pragma unroll
-    for (int q = 0; q < kF32Per; ++q) {
-      const int e = tid + 256 * q, row = e / kF32KS, kk = e % kF32KS;
-      const int ia = rowA0 + row, ib = rowB0 + row;
-      fa[q] = (ia < N && k0 + kk < Dv) ? X[(n0 + ia) * Dv + k0 + kk] : 0.f;
-      fb[q] = (ib < N && k0 + kk < Dv) ? X[(n0 + ib) * Dv + k0 + kk] : 0.f;
-    }
+  const int frow = tid / kF32KS, fk = tid % kF32KS;   // element q of a thread: row frow + kStep q, column fk
+  constexpr int kStep = kF32Threads / kF32KS;
+  auto fetch = [&](int c, int q, float &a, float &b) {
+    const int ia = min(rowA0 + frow + kStep * q, N - 1), ib = min(rowB0 + frow + kStep * q, N - 1);
+    const int k = c * kF32KS + fk;
+    a = X[(n0 + ia) * Dv + min(k, Dv - 1)];
+    b = X[(n0 + ib) * Dv + min(k, Dv - 1)];
   };
-  double acc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
-  double nacc = 0.0;   // wave 0: lane l < 32 row l of A, lane l >= 32 row l - 32 of B
+  // (a use of the loaded value, so it belongs to the stores, not to the loads)
+  auto in_row = [&](int c, float v) { return c * kF32KS + fk < Dv ? v : 0.f; };
+  const int r16 = lane & 15, g = lane >> 4, wa = 16 * (wave >> 1), wb = 16 * (wave & 1);
+  const bool norm_b = wave == 0 || wave == 3;   // waves 0 to 3: the norms of B's low, A's low, A's high, B's high rows
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0}, nacc = {0.0, 0.0, 0.0, 0.0};
   const int nch = (Dv + kF32KS - 1) / kF32KS;
 #pragma unroll
   for (int b = 0; b < kF32Ahead; ++b)
-    if (b < nch) fetch(b * kF32KS, pa[b], pb[b]);
+#pragma unroll
+    for (int q = 0; q < kF32Per; ++q) fetch(min(b, nch - 1), q, pa[b][q], pb[b][q]);
+#pragma unroll
+  for (int q = 0; q < kF32Per; ++q) {
+    sA[0][fk][frow + kStep * q] = in_row(0, pa[0][q]);
+    sB[0][fk][frow + kStep * q] = in_row(0, pb[0][q]);
+  }
+  static_assert(kF32Ahead % 2 == 0, "a chunk's buffer is its parity");
   for (int c0 = 0; c0 < nch; c0 += kF32Ahead) {
 #pragma unroll
     for (int b = 0; b < kF32Ahead; ++b) {
       const int c = c0 + b;
       if (c >= nch) break;
+      const float(&A)[kF32KS][kSub + 1] = sA[b & 1];
+      const float(&B)[kF32KS][kSub + 1] = sB[b & 1];
+      // publishes chunk c; the other buffer's readers (chunk c - 1) are past it
       __syncthreads();
+      // a group: four steps' operands read while the previous four multiply
+      // (two chains, eight matrix instructions), with a share of chunk c + 1's
+      // stores and of chunk c + kF32Ahead's loads
+      constexpr int kGroup = 4, kGroups = kF32KS / 4 / kGroup, kShare = kF32Per / kGroups;
+      constexpr int kNext = kF32Ahead - 1;
+      float fa[2][kGroup], fb[2][kGroup];
+      auto read = [&](int x) {
 #pragma unroll
-      for (int q = 0; q < kF32Per; ++q) {
-        const int e = tid + 256 * q, row = e / kF32KS, kk = e % kF32KS;
-        sA[kk][row] = pa[b][q];
-        sB[kk][row] = pb[b][q];
-      }
-      __syncthreads();
-      if (c + kF32Ahead < nch) fetch((c + kF32Ahead) * kF32KS, pa[b], pb[b]);
-      // full chunks unrolled, so the LDS reads of later columns are issued
-      // while earlier FMAs run; the FMA order along d is the same either way
-      auto mac = [&](int kk) {
-        const double a0 = sA[kk][ty], a1 = sA[kk][ty + 16];
-        const double b0 = sB[kk][tx], b1 = sB[kk][tx + 16];
-        acc[0][0] = fma(a0, b0, acc[0][0]);
-        acc[0][1] = fma(a0, b1, acc[0][1]);
-        acc[1][0] = fma(a1, b0, acc[1][0]);
-        acc[1][1] = fma(a1, b1, acc[1][1]);
-        if (tid < 64) {
-          const double v = tid < 32 ? sA[kk][tid] : sB[kk][tid - 32];
-          nacc = fma(v, v, nacc);
+        for (int u = 0; u < kGroup; ++u) {
+          const int kk = 4 * (x * kGroup + u) + g;
+          fa[x & 1][u] = A[kk][wa + r16];
+          fb[x & 1][u] = B[kk][wb + r16];
         }
       };
-      const int kmax = min(kF32KS, Dv - c * kF32KS);
-      if (kmax == kF32KS) {
+      read(0);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int kk = 0; kk < kF32KS; ++kk) mac(kk);
-      } else {
-        for (int kk = 0; kk < kmax; ++kk) mac(kk);
+      for (int x = 0; x < kGroups; ++x) {
+        if (x + 1 < kGroups) read(x + 1);
+#pragma unroll
+        for (int u = 0; u < kGroup; ++u) {
+          const double da = fa[x & 1][u], db = fb[x & 1][u], dn = norm_b ? db : da;
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(da, db, acc, 0, 0, 0);
+          nacc = __builtin_amdgcn_mfma_f64_16x16x4f64(dn, dn, nacc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int q = x * kShare; q < (x + 1) * kShare; ++q) {
+          sA[1 - (b & 1)][fk][frow + kStep * q] = in_row(c + 1, pa[(b + 1) & kNext][q]);
+          sB[1 - (b & 1)][fk][frow + kStep * q] = in_row(c + 1, pb[(b + 1) & kNext][q]);
+          fetch(min(c + kF32Ahead, nch - 1), q, pa[b][q], pb[b][q]);
+        }
+#pragma unroll
+        for (int u = 0; u < 2 * kGroup; ++u) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+          __builtin_amdgcn_sched_group_barrier(0x380, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
-  if (tid < 64) {
-    const int side = tid >> 5, r = tid & 31;
-    s_nn[side][r] = nacc;
-    s_inv[side][r] = nacc > 0.0 ? 1.0 / sqrt(nacc) : 0.0;
+  // row r16 of the wave's norm operand: element r16 / 4 of the lane with l / 16 = r16 % 4
+  if (g == (r16 & 3)) {
+    double d = 0.0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) d = v == (r16 >> 2) ? nacc[v] : d;
+    const int side = norm_b ? 1 : 0, r = (norm_b ? wb : wa) + r16;
+    s_nn[side][r] = d;
+    s_inv[side][r] = d > 0.0 ? 1.0 / sqrt(d) : 0.0;
     if (self && side == 0 && rowA0 + r < N) {
-      nn[n0 + rowA0 + r] = nacc;
+      nn[n0 + rowA0 + r] = d;
       inv[n0 + rowA0 + r] = s_inv[0][r];
     }
   }
   __syncthreads();
+  // element v of lane l: A row 4 v + l / 16, B column l % 16 of the quadrant
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int il = ty + 16 * a, jl = tx + 16 * b, i = rowA0 + il, j = rowB0 + jl;
-      if (i >= N || j >= N) continue;
-      const float dv = self && i == j ? kSelfMark
-                                      : coverage(acc[a][b], s_nn[0][il], s_nn[1][jl], s_inv[0][il], s_inv[1][jl]);
-      const int64_t oij = cov_index(i, j, nbr), oji = cov_index(j, i, nbr);
-      if (oij < dlim) D[oij] = dv;
-      if (!self && oji < dlim) D[oji] = dv;
-    }
+  for (int v = 0; v < 4; ++v) {
+    const int il = wa + 4 * v + g, jl = wb + r16, i = rowA0 + il, j = rowB0 + jl;
+    if (i >= N || j >= N) continue;
+    const float dv = self && i == j ? kSelfMark
+                                    : coverage(acc[v], s_nn[0][il], s_nn[1][jl], s_inv[0][il], s_inv[1][jl]);
+    const int64_t oij = cov_index(i, j, nbr), oji = cov_index(j, i, nbr);
+    if (oij < dlim) D[oij] = dv;
+    if (!self && oji < dlim) D[oji] = dv;
+  }
 }
 
 }  // namespace
@@ -1101,7 +1257,20 @@ hipError_t launch_similarity(int32_t R, int32_t Dv, last_dtype fdtype, const Sel
   hipError_t e;
   if ((e = launch_gram_plan(R, p, w, cu_vis, s)) != hipSuccess) return e;
 
-  if (fdtype == LAST_BF16) {
+  // Few tiles: one 32 x 32 sub-tile a block, while the grid (16 blocks a tile,
+  // one a compute unit at a time) takes at most three rounds of the chip.
+  // Measured, 128 x 128 tiles / sub-tiles in us, 4096 wide: 36 x 16 blocks
+  // (one request of 1024 tokens) 69 / 61, 45 x 16 (three of 576) 72 / 62, 60 x
+  // 16 (four of 576) 73 / 82; 15 x 16 (one of 576) 60 / 22, at 1536 36 / 12.
+  const bool pairs = fdtype == LAST_BF16 && Dv % 256 == 0 && Dv <= 128 * kPairMaxChunks &&
+                     (p.tiles_diag + p.tiles_off) * kSubs <= 3 * (int64_t)device_cus();
+  if (pairs) {
+    launch_begin("gram", s);
+    hipLaunchKernelGGL(k_gram_pairs, dim3((unsigned)((p.tiles_diag + p.tiles_off) * kSubs)), dim3(kPairThreads), 0, s,
+                       (const uint16_t *)feats, w.dtile, w.otile, w.nn, w.inv, Dv, p.tiles_diag, p.tiles_off,
+                       p.d_elems, w.dmat);
+    if ((e = launch_end(s)) != hipSuccess) return e;
+  } else if (fdtype == LAST_BF16) {
     // the streamed kernel needs a multiple of four 64-column stages; other widths use the staged one
     if (Dv % (4 * kDmaCols) == 0) {
       const int cus = device_cus();
@@ -1132,7 +1301,8 @@ hipError_t launch_similarity(int32_t R, int32_t Dv, last_dtype fdtype, const Sel
   } else {
     // one launch: every block computes its own rows' norms
     launch_begin("gram", s);
-    hipLaunchKernelGGL(k_gram_f32, dim3((unsigned)((p.tiles_diag + p.tiles_off) * kF32Subs)), dim3(256), 0, s,
+    hipLaunchKernelGGL(k_gram_f32, dim3((unsigned)((p.tiles_diag + p.tiles_off) * kSubs)), dim3(kF32Threads), 0,
+                       s,
                        (const float *)feats, w.dtile, w.otile, w.nn, w.inv, Dv, p.tiles_diag, p.tiles_off,
                        p.d_elems, w.dmat);
     if ((e = launch_end(s)) != hipSuccess) return e;

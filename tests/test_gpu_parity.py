@@ -663,3 +663,45 @@ def test_multiblock_wait_timeout_marks_request_invalid():
     _, _, kept2, order2, gains2 = _select_batch(Xs, ws, Ks, W.BF16)
     for x, y in zip((kept0, order0, gains0), (kept2, order2, gains2)):
         assert x.tobytes() == y.tobytes()
+
+
+@pytest.mark.parametrize("dtype,Dv", [("bf16", 256), ("bf16", 4096), ("f32", 4), ("f32", 68), ("f32", 1028)])
+@pytest.mark.parametrize("N", [[1], [31, 33], [576], [16, 17, 128, 129, 250]])
+def test_small_batch_distances(N, dtype, Dv):
+    """Batches whose sub-tiles all run at once (bf16) and fp32 features with
+    widths around the 64-column chunk: every pick's gain against the fp64
+    distances of the whole matrix, duplicates at exactly 0, and the bits of the
+    same requests inside a batch large enough for the 128 x 128 tiles. A gain is
+    w times an fp32 distance whose fp64 sums are within 2^-24 (bf16 chunks of
+    fp32) of the dot's norm product: |gain - exact| <= w 2^-21."""
+    rng = np.random.default_rng(Dv + len(N))
+    total = sum(N)
+    X = rng.standard_normal((total, Dv)).astype(np.float32)
+    X[total // 2] = X[0]
+    if total > 8:
+        X[total - 2] = 0.0
+    feats = torch.from_numpy(X).cuda()
+    feats = feats.bfloat16() if dtype == "bf16" else feats
+    w = torch.from_numpy(rng.random(total).astype(np.float32) + 0.1).cuda()
+    cu = lambda v: np.concatenate([[0], np.cumsum(v)]).astype(np.int32)
+    K = [max(1, n // 2) for n in N]
+    kept, order, gains = last.diverse_select(w, feats, cu(N), cu(K))
+    order, gains = order.cpu().numpy(), gains.cpu().numpy().astype(np.float64)
+    for r, n in enumerate(N):
+        a, k0 = int(cu(N)[r]), int(cu(K)[r])
+        x = feats[a:a + n].double().cpu().numpy()
+        norm = np.linalg.norm(x, axis=1)
+        x = x / np.where(norm > 0, norm, 1.0)[:, None]
+        wr = w[a:a + n].double().cpu().numpy()
+        picks = order[k0:k0 + K[r]]
+        assert len(set(picks)) == K[r]
+        delta = np.full(n, np.inf)
+        for t, j in enumerate(picks):
+            want = wr[j] * (1.0 if t == 0 else delta[j])
+            assert abs(gains[k0 + t] - want) <= wr[j] * 2.0 ** -21, (r, t)
+            delta = np.minimum(delta, np.maximum(0.0, 1.0 - x @ x[j]))
+    if dtype == "bf16":
+        reps = -(-64 * 128 // total) + 1   # enough tiles for the other kernel
+        big = last.diverse_select(w.repeat(reps), feats.repeat(reps, 1), cu(N * reps), cu(K * reps))
+        assert torch.equal(big[1][:len(order)].cpu(), torch.from_numpy(order))
+        assert np.array_equal(big[2][:len(order)].cpu().numpy(), gains.astype(np.float32))
