@@ -90,9 +90,11 @@ hipError_t launch_prefill(const last_batch *b, int64_t QB_total, int32_t *qb_off
 // Query rows are taken 32 at a time (one matrix-core tile). A block of
 // kRowWaves waves takes RT such row tiles (a row group) and splits each stage
 // of keys among the kRowWaves / RT waves that share a row tile; RT is 4, 2 or
-// 1, from the largest request's tile count. Keys go in chunks of kRowChunk.
+// 1, from the largest request's tile count. Keys go in chunks of `chunk`, a
+// multiple of kRowChunk chosen by how many blocks the batch gives.
 constexpr int kRowWaves = 4;
-constexpr int kRowChunk = 1024;
+constexpr int kRowChunk = 1024, kRowChunkMax = 4096;
+constexpr int kRowBlocks = 3;   // blocks per compute unit from which a larger chunk is taken
 
 struct RowsPlan {
   int64_t M_total, N_total, T_total;
@@ -100,6 +102,7 @@ struct RowsPlan {
   int64_t SC_total;         // per layer: sum_r Hq * M_r * key chunks_r row statistics
   int32_t RG_max;           // most row groups of any request
   int32_t RT;               // row tiles per block
+  int32_t chunk;            // keys a block takes, in either pass
   int32_t MB;               // merge blocks per request (256 rows each, for the largest request)
 };
 

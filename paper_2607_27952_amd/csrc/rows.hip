@@ -21,7 +21,7 @@
 //                    each wave multiplies one 32-row query tile by its share of
 //                    every stage. Each lane keeps, for the 16 rows of its
 //                    accumulator, a reference r and the sums of 2^(x - r) over
-//                    all keys and over the visual ones, x being the logit in
+//                    the keys outside and inside the visual span, x being the logit in
 //                    base-2 units (the softmax scale times log2 e folded into
 //                    one multiply). The reference only moves when a logit
 //                    exceeds it by 64 (sums stay far from overflow), so a logit
@@ -55,11 +55,10 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr int kW = last::kRowWaves;
 constexpr int kThreads = 64 * kW;
 constexpr int kSub = 128;                     // keys per LDS stage: four 32-key tiles
-constexpr int kCH = last::kRowChunk;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kSlack = 64.f;                // a reference may trail its row's max by this much
 constexpr float kNoRef = -1e30f;              // the reference of a row that has seen no key yet
-static_assert(kCH % kSub == 0, "whole stages per chunk");
+static_assert(last::kRowChunk % kSub == 0, "whole stages per chunk");
 
 // A key (or query) row of DH elements as 16-byte pieces. One matrix-core step
 // takes one piece from each half of the wave: lanes 0-31 piece 2s, lanes
@@ -240,70 +239,95 @@ __device__ __forceinline__ int wave_min_pos(const int (&prow)[16]) {
 }
 
 // ---------------------------------------------------------------- plan
-__global__ __launch_bounds__(256) void k_rows_plan(
+// One block, 256 requests a pass. Bound by the latency of its dependent loads,
+// so they are few and wide: 16 lanes take a request's rows, 64 requests at a
+// time (a wave a request on four waves: 54 us for 128 requests, now 17).
+constexpr int kPlanThreads = 1024, kPlanReqs = 256;
+__device__ long long block_exclusive_scan_i64(long long v, long long *sh, long long *total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  long long x = v;
+  for (int o = 1; o < 64; o <<= 1) {
+    const long long y = __shfl_up(x, o);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) sh[wave] = x;
+  __syncthreads();
+  long long before = 0, tot = 0;
+#pragma unroll
+  for (int w = 0; w < kPlanThreads / 64; ++w) {
+    if (w < wave) before += sh[w];
+    tot += sh[w];
+  }
+  __syncthreads();
+  *total = tot;
+  return before + x - v;
+}
+
+__global__ __launch_bounds__(kPlanThreads) void k_rows_plan(
     const int32_t *__restrict__ cu_seqlens, const int32_t *__restrict__ vis_start,
     const int32_t *__restrict__ cu_vis, const int32_t *__restrict__ cu_rows,
-    const int32_t *__restrict__ row_pos, int R, int Hq, int g, int RT, int64_t cap1, int64_t cap2,
+    const int32_t *__restrict__ row_pos, int R, int Hq, int g, int RT, int ch, int64_t cap1, int64_t cap2,
     int32_t *__restrict__ off1, int32_t *__restrict__ off2, int64_t *__restrict__ sc_off,
     int4 *__restrict__ rinfo, int4 *__restrict__ items1, int4 *__restrict__ items2) {
-  __shared__ int sh[4];
-  __shared__ long long s_sc[256];
-  __shared__ int s_p1[256], s_p2[256], s_kc[256], s_vc[256], s_rg[256];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ int sh[kPlanThreads / 64];
+  __shared__ long long sh64[kPlanThreads / 64];
+  __shared__ int s_cu[kPlanReqs + 1];
+  __shared__ int s_p1[kPlanReqs], s_p2[kPlanReqs], s_kc[kPlanReqs], s_vc[kPlanReqs], s_rg[kPlanReqs];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int carry1 = 0, carry2 = 0;
   long long carry_sc = 0;
-  for (int base = 0; base < R; base += 256) {
-    const int r = base + (int)threadIdx.x;
-    int n1 = 0, n2 = 0, KC = 0, VC = 0, RG = 0, pmax = 0;
+  for (int base = 0; base < R; base += kPlanReqs) {
+    const int nreq = min(kPlanReqs, R - base), r = base + tid;
+    int n1 = 0, n2 = 0, KC = 0, VC = 0, RG = 0, pmax = 0, N = 0, v0 = 0;
     long long nsc = 0;
-    // each request's last row position: a wave per request, lanes over its rows
-    for (int j = wave; j < min(256, R - base); j += 4) {
-      const int m0 = cu_rows[base + j], M = cu_rows[base + j + 1] - m0;
-      int pm = 0;
-      for (int m = lane; m < M; m += 64) pm = max(pm, row_pos[m0 + m]);
-      pm = (int)wave_max_u32((uint32_t)pm);
-      if (lane == 0) s_kc[j] = pm;
+    if (tid <= nreq) s_cu[tid] = cu_rows[base + tid];
+    if (tid < nreq) {
+      N = cu_vis[r + 1] - cu_vis[r];
+      v0 = vis_start[r];
     }
     __syncthreads();
-    if (r < R) {
-      const int m0 = cu_rows[r], M = cu_rows[r + 1] - m0;
-      pmax = s_kc[threadIdx.x];
+    // each request's last row position
+    for (int j = tid >> 4; j < nreq; j += kPlanThreads / 16) {
+      const int m1 = s_cu[j + 1];
+      int pm = 0;
+#pragma unroll 4
+      for (int m = s_cu[j] + (tid & 15); m < m1; m += 16) pm = max(pm, row_pos[m]);
+#pragma unroll
+      for (int o = 1; o < 16; o <<= 1) pm = max(pm, __shfl_xor(pm, o));
+      if ((tid & 15) == 0) s_kc[j] = pm;
+    }
+    __syncthreads();
+    if (tid < nreq) {
+      const int M = s_cu[tid + 1] - s_cu[tid];
+      pmax = s_kc[tid];
       const int tiles = (g * M + 31) / 32;
       RG = (tiles + RT - 1) / RT;
-      KC = (pmax + 1 + kCH - 1) / kCH;
-      const int N = cu_vis[r + 1] - cu_vis[r];
-      const int seen = min(N, pmax - vis_start[r] + 1);
-      VC = (seen + kCH - 1) / kCH;
+      KC = (pmax + 1 + ch - 1) / ch;
+      const int seen = min(N, pmax - v0 + 1);
+      VC = (seen + ch - 1) / ch;
       n1 = RG * KC;
       n2 = RG * VC;
       nsc = (long long)Hq * M * KC;
       rinfo[r] = make_int4(KC, VC, RG, pmax);
     }
     int t1, t2;
+    long long tsc;
     const int p1 = block_exclusive_scan(n1, sh, &t1) + carry1;
     const int p2 = block_exclusive_scan(n2, sh, &t2) + carry2;
-    // statistics prefix in 64 bits: a plain sequential scan of this pass's 256 counts
-    s_sc[threadIdx.x] = nsc;
-    __syncthreads();
-    long long psc = carry_sc, tsc = 0;
-    for (int i = 0; i < 256; ++i) {
-      if (i < (int)threadIdx.x) psc += s_sc[i];
-      tsc += s_sc[i];
-    }
-    __syncthreads();
-    if (r < R) {
+    const long long psc = block_exclusive_scan_i64(nsc, sh64, &tsc) + carry_sc;
+    if (tid < nreq) {
       off1[r] = p1;
       off2[r] = p2;
       sc_off[r] = psc;
+      s_p1[tid] = p1;
+      s_p2[tid] = p2;
+      s_kc[tid] = KC;
+      s_vc[tid] = VC;
+      s_rg[tid] = RG;
     }
-    s_p1[threadIdx.x] = p1;
-    s_p2[threadIdx.x] = p2;
-    s_kc[threadIdx.x] = KC;
-    s_vc[threadIdx.x] = VC;
-    s_rg[threadIdx.x] = RG;
     __syncthreads();
-    // the work items, chunk-major then row group: a wave per request
-    for (int j = wave; j < min(256, R - base); j += 4) {
+    // the work items, chunk-major then row group: a wave a request
+    for (int j = wave; j < nreq; j += kPlanThreads / 64) {
       const int rg_n = s_rg[j], q1 = s_p1[j], q2 = s_p2[j];
       for (int x = lane; x < s_kc[j] * rg_n; x += 64)
         if (q1 + x < cap1) items1[q1 + x] = make_int4(base + j, x % rg_n, x / rg_n, 0);
@@ -315,7 +339,7 @@ __global__ __launch_bounds__(256) void k_rows_plan(
     carry2 += t2;
     carry_sc += tsc;
   }
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     off1[R] = carry1;
     off2[R] = carry2;
     sc_off[R] = carry_sc;
@@ -330,7 +354,7 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 2 ? 2 : 1) void k_rows_stats
     const int32_t *__restrict__ vis_start, const int32_t *__restrict__ cu_vis,
     const int32_t *__restrict__ cu_rows, const int32_t *__restrict__ row_pos,
     const int4 *__restrict__ items, const int4 *__restrict__ rinfo,
-    const int64_t *__restrict__ sc_off, int64_t n_items, int Hq, int Hkv, int64_t T_total,
+    const int64_t *__restrict__ sc_off, int64_t n_items, int ch, int Hq, int Hkv, int64_t T_total,
     int64_t M_total, int64_t SC_total, float scale2, float4 *__restrict__ stats) {
   using KR = KeyRow<T, DH>;
   constexpr int KS = kW / RT;
@@ -369,13 +393,14 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 2 ? 2 : 1) void k_rows_stats
   }
 
   const int64_t tok0 = cu_seqlens[r];
-  const int kb = c * kCH;
-  const int ke = min(kb + kCH, pmax + 1);
+  const int kb = c * ch;
+  const int ke = min(kb + ch, pmax + 1);
   const int nk = ke - kb;
   const int vlo = vis_start[r], vhi = vlo + (cu_vis[r + 1] - cu_vis[r]);
   const int64_t kstride = (int64_t)Hkv * DH * sizeof(T);
   const char *kbase = (const char *)uniform_ptr(k + (((int64_t)l * T_total + tok0 + kb) * Hkv + kv) * DH);
 
+  // z: the sums over keys outside the visual span, vz: over those inside
   float mr[16], z[16], vz[16];
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
@@ -398,71 +423,65 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 2 ? 2 : 1) void k_rows_stats
       const bool full = s1 <= pmin && s1 < ke;
       const bool allvis = s0 >= vlo && s1 < vhi, novis = s1 < vlo || s0 >= vhi;
       const uint4 *buf = s_k[st & 1];
-      f32x16_t cur, nxt;
-      tile_dots<T, DH>(buf, a, pl.ks, cur);
-      // Per tile: the next tile's matrix-core steps run under this tile's
-      // exponentials. A term whose logit passes its row's reference by more
-      // than the slack is held back and folded in afterwards with a new
-      // reference (rare: the first key a row sees, or a jump of 2^64). The
-      // masked and unmasked loops are separate, so that neither branches.
-      auto fold_big = [&](int j, float vis) {
+      // A stage that every row sees whole and that lies on one side of the
+      // visual span adds its terms to one sum, and only the largest of a
+      // tile's terms is compared with the slack. The next tile's matrix-core
+      // steps run under this tile's exponentials. A tile with a larger term
+      // (rare: the first key a row sees, or a jump of 2^64) adds nothing here.
+      uint32_t todo = (1u << RT) - 1u;   // the wave's tiles left for the checked loop
+      auto run = [&](float (&sum)[16]) {
+        f32x16_t cur, nxt;
+        tile_dots<T, DH>(buf, a, pl.ks, cur);
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+          if (i + 1 < RT) tile_dots<T, DH>(buf, a, pl.ks + KS * (i + 1), nxt);
+          float e[16], top = 0.f;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) e[v] = pow2(fmaf(cur[v], scale2, -mr[v]));
+#pragma unroll
+          for (int v = 0; v < 16; v += 2) top = fmaxf(fmaxf(top, e[v]), e[v + 1]);
+          if (i + 1 < RT) interleave_hint<T, DH, 6>();
+          const bool fits = !__any(!(top < 0x1p64f));
+          todo &= fits ? ~(1u << i) : ~0u;
+          if (fits) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sum[v] += e[v];
+          }
+          if (i + 1 < RT) cur = nxt;
+        }
+      };
+      if (full && allvis)
+        run(vz);
+      else if (full && novis)
+        run(z);
+      // The rest with everything checked: the causal mask, the visual test,
+      // and a term whose logit passes its row's reference by more than the
+      // slack, which gives the row a new reference.
+#pragma unroll 1
+      for (int i = 0; i < RT; ++i) {
+        if (!((todo >> i) & 1u)) continue;
+        f32x16_t cur;
+        tile_dots<T, DH>(buf, a, pl.ks + KS * i, cur);
+        const int j = s0 + (pl.ks + KS * i) * 32 + col;
+        const bool vis = j >= vlo && j < vhi;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const bool live = full || (j <= s_pos[wave][acc_row(lane, v)] && j < ke);
           const float x = cur[v] * scale2;
-          const bool b = live && x - mr[v] > kSlack;
-          const float f = pow2(mr[v] - x);
-          z[v] = b ? fmaf(z[v], f, 1.f) : z[v];
-          vz[v] = b ? fmaf(vz[v], f, vis) : vz[v];
+          const float d = live ? fmaf(cur[v], scale2, -mr[v]) : -INFINITY;
+          const bool b = d > kSlack;
+          const float f = b ? pow2(mr[v] - x) : 1.f, e = b ? 1.f : pow2(d);
+          z[v] = fmaf(z[v], f, vis ? 0.f : e);
+          vz[v] = fmaf(vz[v], f, vis ? e : 0.f);
           mr[v] = b ? x : mr[v];
-        }
-      };
-      if (full) {
-#pragma unroll
-        for (int i = 0; i < RT; ++i) {
-          const int j = s0 + (pl.ks + KS * i) * 32 + col;
-          const float vis = allvis ? 1.f : (novis ? 0.f : ((j >= vlo && j < vhi) ? 1.f : 0.f));
-          if (i + 1 < RT) tile_dots<T, DH>(buf, a, pl.ks + KS * (i + 1), nxt);
-          bool big = false;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const float d = fmaf(cur[v], scale2, -mr[v]);
-            const bool b = d > kSlack;
-            const float e = pow2(b ? -INFINITY : d);
-            z[v] += e;
-            vz[v] = fmaf(e, vis, vz[v]);
-            big |= b;
-          }
-          if (i + 1 < RT) interleave_hint<T, DH, 8>();
-          if (__any(big)) fold_big(j, vis);
-          if (i + 1 < RT) cur = nxt;
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < RT; ++i) {
-          const int j = s0 + (pl.ks + KS * i) * 32 + col;
-          const float vis = (j >= vlo && j < vhi) ? 1.f : 0.f;
-          if (i + 1 < RT) tile_dots<T, DH>(buf, a, pl.ks + KS * (i + 1), nxt);
-          bool big = false;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const bool live = j <= s_pos[wave][acc_row(lane, v)] && j < ke;
-            const float d = live ? fmaf(cur[v], scale2, -mr[v]) : -INFINITY;
-            const bool b = d > kSlack;
-            const float e = pow2(b ? -INFINITY : d);
-            z[v] += e;
-            vz[v] = fmaf(e, vis, vz[v]);
-            big |= b;
-          }
-          if (i + 1 < RT) interleave_hint<T, DH, 10>();
-          if (__any(big)) fold_big(j, vis);
-          if (i + 1 < RT) cur = nxt;
         }
       }
     }
     vm_wait<0>();
     __syncthreads();
   }
+#pragma unroll
+  for (int v = 0; v < 16; ++v) z[v] += vz[v];   // all keys
 
   // merge the 32 lanes of each half (same rows, other keys), then the KS
   // waves that share a row tile, in a fixed order
@@ -547,13 +566,13 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 2 ? 2 : 1) void k_rows_visua
     const T *__restrict__ q, const T *__restrict__ k, const int32_t *__restrict__ cu_seqlens,
     const int32_t *__restrict__ vis_start, const int32_t *__restrict__ cu_vis,
     const int32_t *__restrict__ cu_rows, const int32_t *__restrict__ row_pos,
-    const int4 *__restrict__ items, const int4 *__restrict__ rinfo, int64_t n_items, int Hq,
+    const int4 *__restrict__ items, const int4 *__restrict__ rinfo, int64_t n_items, int ch, int Hq,
     int Hkv, int64_t T_total, int64_t M_total, int64_t N_total, int RG_max, float scale2,
     const float2 *__restrict__ rowstat, float *__restrict__ part) {
   using KR = KeyRow<T, DH>;
   constexpr int KS = kW / RT;
   __shared__ uint4 s_k[2][KR::kStage];
-  __shared__ float s_col[RT][kCH];
+  __shared__ float s_col[2][RT][kSub];   // a stage's sums of each row tile, by stage parity
   // the row groups of one key chunk are neighbouring items: XCD-contiguous
   // numbering runs them on one XCD, where they share the chunk in L2
   const int64_t bid = xcd_contiguous(blockIdx.x, gridDim.x);
@@ -593,8 +612,8 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 2 ? 2 : 1) void k_rows_visua
   const int64_t n0 = cu_vis[r];
   const int N = cu_vis[r + 1] - (int)n0;
   const int seen = min(N, pmax - vlo + 1);
-  const int ib = c * kCH;                        // first visual token of the chunk
-  const int nk = min(kCH, seen - ib);
+  const int ib = c * ch;                         // first visual token of the chunk
+  const int nk = min(ch, seen - ib);
   const int64_t tok0 = cu_seqlens[r];
   const int64_t kstride = (int64_t)Hkv * DH * sizeof(T);
   const char *kbase = (const char *)uniform_ptr(k + (((int64_t)l * T_total + tok0 + vlo + ib) * Hkv + kv) * DH);
@@ -603,6 +622,7 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 2 ? 2 : 1) void k_rows_visua
   stager.issue(0, kbase, kstride, 0, nk);
   vm_wait<0>();
   __syncthreads();
+  float *out = part + (((int64_t)l * Hkv + kv) * RG_max + rg) * N_total + n0 + ib;
   const int nst = (nk + kSub - 1) / kSub;
   for (int st = 0; st < nst; ++st) {
     if (st + 1 < nst) stager.issue((st + 1) & 1, kbase, kstride, (st + 1) * kSub, nk);
@@ -650,16 +670,18 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 2 ? 2 : 1) void k_rows_visua
     }
     if (lane < 32)
 #pragma unroll
-      for (int i = 0; i < RT; ++i) s_col[pl.rt][st * kSub + (pl.ks + KS * i) * 32 + col] = sum[i];
+      for (int i = 0; i < RT; ++i) s_col[st & 1][pl.rt][(pl.ks + KS * i) * 32 + col] = sum[i];
     vm_wait<0>();
     __syncthreads();
-  }
-  float *out = part + (((int64_t)l * Hkv + kv) * RG_max + rg) * N_total + n0 + ib;
-  for (int t = threadIdx.x; t < nk; t += kThreads) {
-    float x = s_col[0][t];
+    // the stage's keys, summed over the row tiles (the buffer is written again
+    // two stages on, past the next barrier)
+    const int t = st * kSub + (int)threadIdx.x;
+    if (threadIdx.x < kSub && t < nk) {
+      float x = s_col[st & 1][0][threadIdx.x];
 #pragma unroll
-    for (int w = 1; w < RT; ++w) x += s_col[w][t];
-    out[t] = x;
+      for (int w = 1; w < RT; ++w) x += s_col[st & 1][w][threadIdx.x];
+      out[t] = x;
+    }
   }
 }
 
@@ -701,7 +723,7 @@ hipError_t launch_passes(const last_batch *b, const last::RowsPlan &p, const las
   last::launch_begin("rows_stats", s);
   hipLaunchKernelGGL((k_rows_stats<T, DH, RT>), dim3((unsigned)blocks1), dim3(kThreads), 0, s,
                      (const T *)q, (const T *)k, b->cu_seqlens, b->vis_start, b->cu_vis, cu_rows,
-                     row_pos, w.items1, w.rinfo, w.sc_off, p.items1, b->Hq, b->Hkv, p.T_total,
+                     row_pos, w.items1, w.rinfo, w.sc_off, p.items1, p.chunk, b->Hq, b->Hkv, p.T_total,
                      p.M_total, p.SC_total, scale2, w.stats);
   hipError_t e = last::launch_end(s);
   if (e != hipSuccess) return e;
@@ -716,7 +738,7 @@ hipError_t launch_passes(const last_batch *b, const last::RowsPlan &p, const las
   last::launch_begin("rows_visual", s);
   hipLaunchKernelGGL((k_rows_visual<T, DH, RT>), dim3((unsigned)blocks2), dim3(kThreads), 0, s,
                      (const T *)q, (const T *)k, b->cu_seqlens, b->vis_start, b->cu_vis, cu_rows,
-                     row_pos, w.items2, w.rinfo, p.items2, b->Hq, b->Hkv, p.T_total, p.M_total,
+                     row_pos, w.items2, w.rinfo, p.items2, p.chunk, b->Hq, b->Hkv, p.T_total, p.M_total,
                      p.N_total, p.RG_max, scale2, w.rowstat, w.part);
   return last::launch_end(s);
 }
@@ -746,22 +768,39 @@ RowsPlan make_rows_plan(const last_batch *b, const int32_t *cu_rows_h, const int
   for (int r = 0; r < b->R; ++r)
     max_tiles = std::max(max_tiles, (g * (cu_rows_h[r + 1] - cu_rows_h[r]) + 31) / 32);
   p.RT = max_tiles >= 3 ? 4 : max_tiles;
+  // The largest chunk that still gives every compute unit kRowBlocks blocks
+  // (two run at a time): a block's start and end (its dependent loads, the
+  // merge of its lanes) cost as much as some 1000 keys. Both passes, always
+  // 1024 keys / this rule, us: 8 x 16512 tokens, 4 layers 1431 / 1130; 32 x
+  // 2976 306 / 258; 128 ragged requests of 288 to 16640 809 / 645; 64 x 640
+  // and single requests keep 1024 (384, 71).
+  constexpr int kSizes = 3;
+  static_assert(kRowChunk << (kSizes - 1) == kRowChunkMax, "chunks double");
+  int64_t n1[kSizes] = {}, n2[kSizes] = {}, sc[kSizes] = {};
   for (int r = 0; r < b->R; ++r) {
     const int M = cu_rows_h[r + 1] - cu_rows_h[r];
-    int pmax = 0;
-    for (int m = 0; m < M; ++m) pmax = std::max(pmax, row_pos_h[cu_rows_h[r] + m]);
     const int tiles = (g * M + 31) / 32;
     const int RG = (tiles + p.RT - 1) / p.RT;
-    const int KC = (pmax + 1 + kRowChunk - 1) / kRowChunk;
+    int pmax = 0;
+    for (int m = cu_rows_h[r]; m < cu_rows_h[r + 1]; ++m) pmax = std::max(pmax, row_pos_h[m]);
     const int N = b->cu_vis_h[r + 1] - b->cu_vis_h[r];
     const int seen = std::min(N, pmax - b->vis_start_h[r] + 1);
-    const int VC = (seen + kRowChunk - 1) / kRowChunk;
-    p.items1 += (int64_t)RG * KC;
-    p.items2 += (int64_t)RG * VC;
-    p.SC_total += (int64_t)b->Hq * M * KC;
+    for (int i = 0; i < kSizes; ++i) {
+      const int ch = kRowChunk << i;
+      const int KC = (pmax + 1 + ch - 1) / ch, VC = (seen + ch - 1) / ch;
+      n1[i] += (int64_t)RG * KC;
+      n2[i] += (int64_t)RG * VC;
+      sc[i] += (int64_t)b->Hq * M * KC;
+    }
     p.RG_max = std::max(p.RG_max, RG);
     p.MB = std::max<int32_t>(p.MB, (int32_t)(((int64_t)b->G * b->Hq * M + 255) / 256));
   }
+  int i = kSizes - 1;
+  while (i > 0 && (int64_t)b->G * b->Hkv * n1[i] < kRowBlocks * (int64_t)device_cus()) --i;
+  p.chunk = kRowChunk << i;
+  p.items1 = n1[i];
+  p.items2 = n2[i];
+  p.SC_total = sc[i];
   return p;
 }
 
@@ -788,8 +827,8 @@ hipError_t launch_rows(const last_batch *b, const RowsPlan &p, const RowsWs &w,
                        const void *k, float *scores, float scale, hipStream_t s) {
   const int g = b->Hq / b->Hkv;
   launch_begin("rows_plan", s);
-  hipLaunchKernelGGL(k_rows_plan, dim3(1), dim3(256), 0, s, b->cu_seqlens, b->vis_start, b->cu_vis,
-                     cu_rows, row_pos, b->R, b->Hq, g, p.RT, p.items1, p.items2, w.off1, w.off2,
+  hipLaunchKernelGGL(k_rows_plan, dim3(1), dim3(kPlanThreads), 0, s, b->cu_seqlens, b->vis_start, b->cu_vis,
+                     cu_rows, row_pos, b->R, b->Hq, g, p.RT, p.chunk, p.items1, p.items2, w.off1, w.off2,
                      w.sc_off, w.rinfo, w.items1, w.items2);
   hipError_t e = launch_end(s);
   if (e != hipSuccess) return e;

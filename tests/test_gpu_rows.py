@@ -180,3 +180,38 @@ def test_config_sources(name, src, full):
     w = orc_rows(sub, cu_o, pos_o, q_o)
     got = np.concatenate([g[wl.cu_vis[r]:wl.cu_vis[r + 1]] for r in samples])
     assert_scores(got, w, f"{name} {src} requests {samples}")
+
+
+@pytest.mark.parametrize("dtype,Dh", [("bf16", 128), ("bf16", 64), ("f32", 64)])
+def test_rows_long_chunks(dtype, Dh):
+    """Enough requests for chunks of 4096 keys: lengths around the 128-key stage
+    and the chunk, visual spans that start and end inside a stage, rows before
+    the last position, and keys far above the first ones (the reference moves).
+    Against fp64 softmax rows at the 1e-5 score bar; the fp32 logits of the
+    raised keys (up to 50) add 50 2^-22."""
+    rng = np.random.default_rng(Dh)
+    R, G, Hq, Hkv = 130, 1, 8, 8
+    N = np.concatenate([[1, 127, 128, 129, 1023, 1024, 1025, 4095, 4096, 4100, 5000, 8200],
+                        rng.integers(2, 700, R - 12)])
+    pre, post = rng.integers(0, 140, R), rng.integers(1, 20, R)
+    P = N + pre + post
+    cu = np.concatenate([[0], np.cumsum(P)]).astype(np.int32)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator("cuda").manual_seed(Dh)
+    k = torch.randn((G, int(cu[-1]), Hkv, Dh), device="cuda", generator=gen)
+    k[0, cu[:-1] + P // 2] *= 12.0
+    k = k.to(dt)
+    pos = [np.unique(np.append(rng.integers(pre[r], P[r], 2), P[r] - 1)) for r in range(R)]
+    cr = np.concatenate([[0], np.cumsum([len(x) for x in pos])]).astype(np.int32)
+    q = torch.randn((G, int(cr[-1]), Hq, Dh), device="cuda", generator=gen).to(dt)
+    b = last.Batch.make(G, Hq, Hkv, Dh, cu, pre.astype(np.int32), np.concatenate([[0], np.cumsum(N)]).astype(np.int32))
+    got = last.rows_scores(b, last.Rows.make(cr, np.concatenate(pos).astype(np.int32)), q, k).double()
+    a = 0
+    for r in range(R):
+        z = torch.einsum("mhd,phd->hmp", q[0, cr[r]:cr[r + 1]].double(), k[0, cu[r]:cu[r + 1]].double()) * Dh ** -0.5
+        see = torch.arange(int(P[r]), device="cuda")[None] <= torch.from_numpy(pos[r]).cuda()[:, None]
+        p = torch.softmax(z.masked_fill(~see, -torch.inf), -1).sum((0, 1))[pre[r]:pre[r] + N[r]]
+        want = p / p.sum()
+        g = got[a:a + N[r]]
+        a += int(N[r])
+        assert torch.all((g - want).abs() <= (1e-5 + 50 * 2.0 ** -22) * want + 2.0 ** -110), f"request {r}: {N[r]} tokens"
