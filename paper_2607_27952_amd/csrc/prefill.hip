@@ -33,7 +33,7 @@
 //                  exactly the keys its half of the B operand needs.
 // The softmax runs online per lane in base-2 units (the scale times log2 e
 // folded into the exponent's fma) against a per-query reference that is the
-// first unit's largest logit and moves only when a unit's terms pass 2^64, so
+// first unit's largest logit and moves only when a unit's terms pass 2^16, so
 // the common path has no maximum, no exchange between lanes and no rescaling.
 //
 // What bounds it: the matrix cores at the clock the part's power allows. The
@@ -58,8 +58,10 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr int kKS = 64;                       // keys per LDS stage: two units of 32
 constexpr float kLog2e = 1.4426950408889634f;
-// The sum of one unit's terms past which a query's reference moves.
-constexpr float kMoveAt = 0x1p64f;
+// The sum of one unit's terms past which a query's reference moves: far above
+// what ordinary rows reach past their first unit, and low enough that the sums
+// of values up to 2^90 stay finite (with 2^64, values past 2^49 could overflow).
+constexpr float kMoveAt = 0x1p16f;
 
 constexpr int kNW = 4;                        // waves a block, of 32 query positions each
 constexpr int kThreads = 64 * kNW, kQB = 32 * kNW;

@@ -191,11 +191,12 @@ def _f64_prefill(q, k, v, cu, scale):
 
 
 @pytest.mark.parametrize("Dh", [64, 128])
-@pytest.mark.parametrize("kind", ["rising", "spikes", "low"])
+@pytest.mark.parametrize("kind", ["rising", "spikes", "low", "large"])
 def test_prefill_moving_reference(Dh, kind):
     """Logits that leave the reference of the first keys behind: rising by
     hundreds of powers of two along the sequence, single keys far above the
-    rest, and all far below zero. Lengths around the 32-key units, the 64-key
+    rest, all far below zero, and rising under values of 2^80 (sums against a
+    reference left far behind would overflow). Lengths around the 32-key units, the 64-key
     stages and the 128-query blocks. The bar is the module's: 2^-8 V for the
     rounded probabilities, 2^-8 of the output and the fp32 sums, with V = max
     |v| over the row's keys."""
@@ -207,8 +208,9 @@ def test_prefill_moving_reference(Dh, kind):
     q, k, v = rnd(1, T, Hq, Dh), rnd(1, T, Hkv, Dh), rnd(1, T, Hkv, Dh).bfloat16()
     q[..., 0], k[..., 0] = 8.0, 0.0
     pos = torch.cat([torch.arange(n, device="cuda") for n in P])
-    if kind == "rising":
+    if kind in ("rising", "large"):
         k[0, :, :, 0] = (pos * 2.0)[:, None]
+        v = v * (2.0 ** 80 if kind == "large" else 1.0)
     elif kind == "spikes":
         k[0, pos % 37 == 36, :, 0] = 300.0
         k[0, pos % 101 == 100, :, 0] = 900.0
