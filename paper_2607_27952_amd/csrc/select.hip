@@ -795,10 +795,13 @@ static void greedy_shape(int32_t n, int32_t nreq, int32_t budget, int32_t *threa
 //     each a chain of select, candidate distances, greedy and fold.
 // Fitted on uniform batches of 256 to 16384 tokens, 1 to 128 requests, three
 // widths, both kinds of relevance (deviation about 25%); the rounds are taken
-// at 0.9 of the matrix's estimate. Measured either side (matrix / rounds,
-// us): 32 x 2880 tokens, 4096 wide, 1/9 kept: 1941 / 1127 (uniform relevance
-// 1973); 64 x 576: 245 / 417; 8 x 4096, 3584 wide, 1/16: 988 / 741 (1461
-// uniform); 128 ragged requests of 256 to 16384, 1536 wide, 1/8: 12980 /
+// at 0.9 of the matrix's estimate. Where that holds they measured 1.15 to 5
+// times faster on peaked relevance and 0.75 (128 x 1024 tokens) to 3 times on
+// uniform relevance, which the host cannot tell apart. Measured either side
+// (matrix / rounds, us): 32 x 2880 tokens, 4096 wide, 1/9 kept: 1941 / 1127
+// (uniform relevance 1973; 1904 / 2161 where it deviates by 1% only); 64 x
+// 576: 245 / 417; 8 x 4096, 3584 wide, 1/16: 988 / 741 (1461 uniform; the
+// matrix stays); 128 ragged requests of 256 to 16384, 1536 wide, 1/8: 12980 /
 // 4960. A larger budget needs more rounds and the same matrix, so the form
 // depends on the budgets, and the workspace is the matrix form's.
 static bool rounds_estimate(int32_t R, const int32_t *cu_vis_h, const int32_t *cu_keep_h, int32_t Dv) {
