@@ -32,17 +32,22 @@
 //                  the permutation above makes each lane's probabilities
 //                  exactly the keys its half of the B operand needs.
 // The softmax runs online per lane in base-2 units (the scale times log2 e
-// folded into the exponent's fma) against a per-query reference that is the
-// first unit's largest logit and moves only when a unit's terms pass 2^16, so
-// the common path has no maximum, no exchange between lanes and no rescaling.
+// folded into the exponent's fma): a stage of 64 keys at a time, its maximum
+// first, so that every probability is at most 1, a row's largest exactly 1,
+// and the sums stay as finite as the values; what was summed is rescaled only
+// when some lane's maximum has moved.
 //
 // What bounds it: the matrix cores at the clock the part's power allows. The
-// loop is pipelined by units of 32 keys (logits of the next unit and values
-// of the previous one on the matrix cores while the vector ALU forms this
-// one's probabilities). 8 x 16512 tokens, 28/4 heads, one layer: 23.5 ms with
-// the stage-serial loop, 14.7 now (1.07 PFLOP/s at 1.8 GHz, where torch's
-// 8192^3 product reaches 1.22); without the bank
-// swizzle below, 16.5. 64 x 640 tokens, 32 heads, 2 layers: 1.26 -> 0.87 ms.
+// loop is pipelined by stages: the matrix cores form the next stage's logits
+// and then this stage's products with the values while the vector ALU forms
+// this stage's probabilities, and the next stage's maximum is taken under the
+// last products. 8 x 16512 tokens, 28/4 heads, one layer: 23.1 ms with the
+// same arithmetic one phase after the other, 14.9 now (1.05 PFLOP/s, where
+// torch's 8192^3 product reaches 1.22). 64 x 640 tokens, 32 heads, 2 layers:
+// 1.27 -> 0.88 ms. A reference that moves only past 2^16 instead of the
+// maximum took 14.5 and 0.87 ms, but rounds a row's largest probability and
+// lets values past 2^90 overflow. With the products one stage behind, the
+// registers spill (20.3 and 1.45 ms).
 #include <algorithm>
 #include <math.h>
 #include <type_traits>
@@ -58,10 +63,6 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr int kKS = 64;                       // keys per LDS stage: two units of 32
 constexpr float kLog2e = 1.4426950408889634f;
-// The sum of one unit's terms past which a query's reference moves: far above
-// what ordinary rows reach past their first unit, and low enough that the sums
-// of values up to 2^90 stay finite (with 2^64, values past 2^49 could overflow).
-constexpr float kMoveAt = 0x1p16f;
 
 constexpr int kNW = 4;                        // waves a block, of 32 query positions each
 constexpr int kThreads = 64 * kNW, kQB = 32 * kNW;
@@ -73,9 +74,8 @@ struct Shape {
   static constexpr int kSteps = kPieces / 2;             // S^T MFMA steps per key tile
   static constexpr int kDT = DH / 32;                    // value-dimension tiles of O^T
   static constexpr int kDma = kKS * kPieces / 64 / kNW;  // DMA instructions per operand stage and wave
-  static constexpr int kPairs = 8 / kSteps;              // probability pairs a chunk (a chunk: one S^T step)
   static_assert(kKS * kPieces % (64 * kNW) == 0, "stage split");
-  static_assert(kSteps == 2 * kDT && 8 % kSteps == 0, "chunk split");
+  static_assert(kSteps == 2 * kDT, "chunk split");
 };
 
 // Physical 16-byte piece of logical piece p in row j of a stage (keys and
@@ -117,15 +117,20 @@ __device__ __forceinline__ float half_max(float v) {
   const u32x2_t r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-__device__ __forceinline__ float half_sum(float v) { return v + __shfl_xor(v, 32); }
+__device__ __forceinline__ float half_sum(float v) {
+  typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+  const u32x2_t r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 
 // The request's last row against its visual keys (the first of them at kp):
 // its logits again (the same products, bit for bit, with that row in every
 // column and the keys straight from memory, mostly from L2), written in the
-// score pass's base-2 units, and the sum of their terms against the reference
-// mr, of this wave's share. One tile's keys are in flight; with four, the
+// score pass's base-2 units, and the sum of their terms against the row's
+// maximum mr, of this wave's share. One tile's keys are in flight; with four, the
 // attention loop above it lost its registers to them (64 x 640 tokens: 1003
-// -> 1114 us, and 1070 as a call of its own).
+// -> 1114 us, and 1070 as a call of its own); inside the loop, beside the row's
+// own stages, it costs every wave registers too (893 -> 1009 us).
 template <int DH>
 __device__ __forceinline__ float last_row(const uint16_t *qrow, const uint16_t *kp, int64_t kvstride, int nvis,
                                           float s2, float mr, float *vl, int Hq) {
@@ -240,7 +245,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_prefill(
               (uint32_t)min(kRows * x + drow, kend - 1 - st * kKS) * rowb + dpiece);
     }
   };
-  // group g: the keys and values that step g of the loop below reads
+  // group g: the keys and values that stage g of the loop below reads
   auto issue_group = [&](int g) {
     if (g + 1 < nst) issue(kbase, s_k[(g + 1) % kRing], g + 1);
     if (g < nst) issue(vbase, s_v[g % kRing], g);
@@ -276,62 +281,42 @@ __global__ __launch_bounds__(kThreads, 2) void k_prefill(
     return __builtin_bit_cast(bf16x8_t, av);
   };
 
-  // Per lane (= per query): the reference m of the exponentials (base-2
-  // units) and the sum. The lane's terms cover its half's keys; the halves are
-  // added at the end.
+  // Per lane (= per query), in both halves alike: the running maximum m of the
+  // stages so far (base-2 units) and the sum of the terms against it.
   float m = -INFINITY, lsum = 0.f;
   f32x16_t o[SH::kDT];
 #pragma unroll
   for (int dt = 0; dt < SH::kDT; ++dt) o[dt] = f32x16_t{};
 
-  // keys a query does not see (causal mask, past the block's end) are -inf
-  auto mask = [&](f32x16_t &sc, int u) {
-    if (32 * u + 31 <= q0) return;   // every query of the wave sees every key
+  // The maximum with stage j (logits in x, whose keys a query does not see
+  // become -inf), what its exponents subtract, the factor of the sums so far,
+  // and whether any query's maximum moved. (s2 > 0, so the largest dot gives
+  // the largest logit. A query with no key seen yet keeps -inf; its terms and
+  // sums are 0.)
+  float mref = 0.f, alpha = 1.f;
+  bool moved = false;
+  auto maximum = [&](f32x16_t (&x)[2], int j) {
+    if (kKS * j + kKS - 1 > q0) {   // causal mask, and past the block's end
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int key = 32 * u + acc_key(half, e);
-      sc[e] = (key <= qpos && key < kend) ? sc[e] : -INFINITY;
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int key = kKS * j + 32 * t + acc_key(half, e);
+          x[t][e] = (key <= qpos && key < kend) ? x[t][e] : -INFINITY;
+        }
     }
-  };
-  // Probabilities of elements 2 i and 2 i + 1, packed: the raw dots stay in
-  // place and the scale goes into the exponent.
-  auto pair = [&](const f32x16_t &sc, uint32_t (&pb)[8], float &ps, float mr, int i) {
-    const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[2 * i], s2, -mr));
-    const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[2 * i + 1], s2, -mr));
-    ps += p0 + p1;
-    pb[i] = pack_bf16(p0, p1);
-  };
-  auto ref = [](float x) { return x == -INFINITY ? 0.f : x; };
-  // What remains of a unit's softmax once its terms are there. If they passed
-  // kMoveAt (or are not numbers, or it is the first unit), move the reference
-  // to the largest logit, rescale what was summed against the old one and form
-  // the terms again. (s2 > 0, so the largest dot gives the largest logit. A
-  // query with no key seen yet keeps -inf; its terms and sums are 0.)
-  auto close = [&](const f32x16_t &sc, uint32_t (&pb)[8], float &ps, bool first) {
-    if (first || __any(!(ps < kMoveAt))) {
-      float mx = sc[0];
+    float mx = x[0][0];
 #pragma unroll
-      for (int e = 1; e < 16; ++e) mx = fmaxf(mx, sc[e]);
-      const float mnew = fmaxf(m, half_max(mx) * s2), mr = ref(mnew);
-      const float alpha = __builtin_amdgcn_exp2f(m - mr);
-      m = mnew;
-      lsum *= alpha;
-      ps = 0.f;
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int dt = 0; dt < SH::kDT; ++dt) o[dt] *= alpha;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) pair(sc, pb, ps, mr, i);
-    }
-    lsum += ps;
-  };
-  auto bfrag = [&](const uint32_t (&pb)[8], int s) {
-    return __builtin_bit_cast(bf16x8_t, make_uint4(pb[4 * s], pb[4 * s + 1], pb[4 * s + 2], pb[4 * s + 3]));
+      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, x[t][e]);
+    const float mnew = fmaxf(m, half_max(mx) * s2);
+    mref = mnew == -INFINITY ? 0.f : mnew;
+    alpha = __builtin_amdgcn_exp2f(m - mref);
+    moved = __any(mnew != m);
+    m = mnew;
   };
 
-  // The loop is pipelined by units of 32 keys: while the vector ALU forms
-  // unit u's probabilities, the matrix cores form unit u + 1's logits and add
-  // unit u - 1's probabilities times the values. Step j takes units 2 j + 1
-  // and 2 j + 2, which read the keys of stage j + 1 and the values of stage j.
   issue(kbase, s_k[0], 0);
   issue_group(0);
   if (nst > 1)
@@ -339,91 +324,126 @@ __global__ __launch_bounds__(kThreads, 2) void k_prefill(
   else
     vm_wait<0>();
   __syncthreads();
-  f32x16_t sa, sb;
-  uint32_t pa[8], pn[8];
+  f32x16_t sc[2][2];   // logits of a stage's two 32-key tiles, by stage parity
   if (wst > 0) {
     const uint16_t *ks = reinterpret_cast<const uint16_t *>(s_k[0]);
-    sa = sb = f32x16_t{};
+    sc[0][0] = sc[0][1] = f32x16_t{};
 #pragma unroll
-    for (int s = 0; s < SH::kSteps; ++s) {
-      sb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag(ks, 0, s), bq[s], sb, 0, 0, 0);
-      sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag(ks, 1, s), bq[s], sa, 0, 0, 0);
-    }
-    mask(sb, 0);
-    float ps = 0.f;
-    close(sb, pa, ps, true);
-    mask(sa, 1);
+    for (int s = 0; s < SH::kSteps; ++s)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        sc[0][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag(ks, t, s), bq[s], sc[0][t], 0, 0, 0);
+    maximum(sc[0], 0);
   }
-  // One unit: softmax of `cur` into pnew, the logits of the next unit into
-  // `next` (key tile t of ks), and the values of 16-key steps 2 t, 2 t + 1 of
-  // vs times pold. A chunk is a key and a value fragment from LDS (read two
-  // chunks ahead), an MFMA of each product and a share of the probabilities.
-  auto unit = [&](auto logits, f32x16_t &cur, f32x16_t &next, const uint32_t (&pold)[8], uint32_t (&pnew)[8],
-                  const uint16_t *ks, const uint16_t *vs, int t) {
+  // Stage j (slot S = j % 2) in chunks of one MFMA: the logits of stage j + 1
+  // (if LOGITS), then the stage's probabilities times the values, 16 keys at a
+  // time; the probabilities are formed beside both, a pair every 1.6 chunks at
+  // DH = 128, so that each group of 16 keys is there before its products. A
+  // chunk's fragment is read from LDS two chunks ahead.
+  auto body = [&](auto logits, auto parity, int j, int vslot) {
     constexpr bool LOGITS = decltype(logits)::value;
-    bf16x8_t kf[3], vf[3];
-    const float mr = ref(m);
-    float ps = 0.f;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      if (LOGITS) kf[i] = kfrag(ks, t, i);
-      vf[i] = vfrag(vs, 2 * t + i / SH::kDT, i % SH::kDT);
-    }
-#pragma unroll
-    for (int c = 0; c < SH::kSteps; ++c) {
-      if (c + 2 < SH::kSteps) {
-        if (LOGITS) kf[(c + 2) % 3] = kfrag(ks, t, c + 2);
-        vf[(c + 2) % 3] = vfrag(vs, 2 * t + (c + 2) / SH::kDT, (c + 2) % SH::kDT);
+    constexpr int S = decltype(parity)::value, kHalf = 2 * SH::kSteps, kChunks = 2 * kHalf;
+    constexpr int kDone = 15 * kChunks / 20;   // the chunk with the last probabilities
+    const uint16_t *ks = reinterpret_cast<const uint16_t *>(s_kv[0][1 - S]);
+    const uint16_t *vs = reinterpret_cast<const uint16_t *>(s_kv[1][vslot]);
+    f32x16_t(&cur)[2] = sc[S], (&next)[2] = sc[1 - S];
+    uint32_t pb[16];
+    bf16x8_t fr[3];
+    auto read = [&](int c) {
+      if (c < kHalf) {
+        if (LOGITS) fr[c % 3] = kfrag(ks, c / SH::kSteps, c % SH::kSteps);
+      } else {
+        fr[c % 3] = vfrag(vs, (c - kHalf) / SH::kDT, (c - kHalf) % SH::kDT);
       }
-      if (LOGITS)
-        next = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[c % 3], bq[c], c == 0 ? f32x16_t{} : next, 0, 0, 0);
-      o[c % SH::kDT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[c % 3], bfrag(pold, c / SH::kDT), o[c % SH::kDT],
-                                                               0, 0, 0);
+    };
+    float ps = 0.f;
+    read(0);
+    read(1);
 #pragma unroll
-      for (int x = 0; x < SH::kPairs; ++x) pair(cur, pnew, ps, mr, c * SH::kPairs + x);
-      __builtin_amdgcn_sched_barrier(0);
+    for (int c = 0; c < kChunks; ++c) {
+      if (c + 2 < kChunks) read(c + 2);
+      // the maximum moves rarely after the first stages: rescale only then
+      if (c == kHalf && moved) {
+#pragma unroll
+        for (int dt = 0; dt < SH::kDT; ++dt) o[dt] *= alpha;
+      }
+      if (c >= kHalf) {
+        const int s = (c - kHalf) / SH::kDT;
+        f32x16_t &od = o[(c - kHalf) % SH::kDT];
+        od = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            fr[c % 3],
+            __builtin_bit_cast(bf16x8_t, make_uint4(pb[4 * s], pb[4 * s + 1], pb[4 * s + 2], pb[4 * s + 3])), od, 0, 0, 0);
+      } else if (LOGITS) {
+        f32x16_t &n = next[c / SH::kSteps];
+        n = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[c % 3], bq[c % SH::kSteps],
+                                                    c % SH::kSteps == 0 ? f32x16_t{} : n, 0, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        if (i * kChunks / 20 != c) continue;
+        const f32x16_t &x = cur[i / 8];
+        const int e = 2 * (i % 8);
+        // the raw dots stay in place and the scale goes into the exponent
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(x[e], s2, -mref));
+        const float p1 = __builtin_amdgcn_exp2f(fmaf(x[e + 1], s2, -mref));
+        ps += p0 + p1;
+        pb[i] = pack_bf16(p0, p1);
+      }
+      // (after that chunk the maximum's steps go among the remaining products)
+      if (c == kDone) {
+        lsum = fmaf(lsum, alpha, half_sum(ps));
+        if (LOGITS) maximum(next, j + 1);
+      }
+      if (c < kDone) __builtin_amdgcn_sched_barrier(0);
     }
-    close(cur, pnew, ps, false);
+    static_assert(kDone < kHalf + 3 * SH::kDT && 11 * kChunks / 20 < kHalf + 2 * SH::kDT &&
+                      7 * kChunks / 20 < kHalf + SH::kDT && 3 * kChunks / 20 < kHalf,
+                  "probabilities before their products");
   };
-  // (steps in pairs, so that the ring slots, and with them every fragment's
-  // address but the lane's part, are constants)
-  static_assert(kRing == 2, "slot parity");
-  auto step = [&](auto parity, int j) {
-    constexpr int kSlot = decltype(parity)::value;   // j % 2
-    // group j has landed for this wave; the barrier publishes it and retires
-    // every read of the slots group j + 1 overwrites
+  // Every wave of the block passes turn(0) .. turn(nst - 1). At turn(j) the
+  // keys of stage j + 1 and the values of stage j have landed for this wave;
+  // the barrier publishes them and retires every read of the slots that the
+  // next group overwrites.
+  auto turn = [&](int j) {
     vm_wait<0>();
     __syncthreads();
     issue_group(j + 1);
-    const uint16_t *ks = reinterpret_cast<const uint16_t *>(s_kv[0][1 - kSlot]);
-    const uint16_t *vs = reinterpret_cast<const uint16_t *>(s_kv[1][kSlot]);
-    if (j + 1 < wst) {
-      unit(std::true_type{}, sa, sb, pa, pn, ks, vs, 0);
-      mask(sb, 2 * j + 2);
-      unit(std::true_type{}, sb, sa, pn, pa, ks, vs, 1);
-      mask(sa, 2 * j + 3);
-    } else if (j + 1 == wst) {
-      unit(std::false_type{}, sa, sb, pa, pn, ks, vs, 0);
-#pragma unroll
-      for (int c = 0; c < SH::kSteps; ++c)
-        o[c % SH::kDT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfrag(vs, 2 + c / SH::kDT, c % SH::kDT),
-                                                                 bfrag(pn, c / SH::kDT), o[c % SH::kDT], 0, 0, 0);
-    }
   };
-  for (int j = 0; j < nst; j += 2) {
-    step(std::integral_constant<int, 0>{}, j);
-    if (j + 1 < nst) step(std::integral_constant<int, 1>{}, j + 1);
+  // Stages in pairs, so that the ring slots, and with them every fragment's
+  // address but the lane's part, are constants.
+  static_assert(kRing == 2, "slot parity");
+  constexpr std::true_type more{};
+  constexpr std::false_type final{};
+  constexpr std::integral_constant<int, 0> even{};
+  constexpr std::integral_constant<int, 1> odd{};
+  int j = 0;
+  if (wst > 0) {
+    for (; j + 2 < wst; j += 2) {
+      turn(j);
+      body(more, even, j, 0);
+      turn(j + 1);
+      body(more, odd, j + 1, 1);
+    }
+    if (j + 1 < wst) {
+      turn(j);
+      body(more, even, j++, 0);
+      sc[0][0] = sc[1][0];
+      sc[0][1] = sc[1][1];
+    }
+    turn(j);
+    body(final, even, j, j % kRing);   // the logits are in sc[0] either way
+    ++j;
   }
+  for (; j < nst; ++j) turn(j);
 
   // out_p = O^T column / sum; lane half h holds dimensions 4 h + e % 4 + 8 (e /
   // 4) of its query. The wave's 32 rows go through LDS (free once every wave
   // is past its last read; rows of NP 16-byte pieces, swizzled like a stage)
   // and leave as whole rows.
   __syncthreads();
-  const float lall = half_sum(lsum);
   if (wst > 0) {
     uint4 *rows = &s_kv[0][0][0] + wave * 32 * NP;
-    const float inv = 1.0f / lall;
+    const float inv = 1.0f / lsum;
 #pragma unroll
     for (int dt = 0; dt < SH::kDT; ++dt)
 #pragma unroll
@@ -449,7 +469,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_prefill(
   __shared__ float s_last[2], s_vsum[kNW];
   if (q0 <= P - 1 && P - 1 < q0 + 32 && qpos == P - 1 && half == 0) {
     s_last[0] = m;
-    s_last[1] = lall;
+    s_last[1] = lsum;
   }
   __syncthreads();
   const float mlast = s_last[0];

@@ -241,3 +241,33 @@ def test_prefill_moving_reference(Dh, kind):
         tol = 1e-5 + 8.0 * 900.0 / np.sqrt(Dh) * 2.0 ** -22 * 8
         floor = Hq * 2.0 ** -125 / float(s.sum())
         assert torch.all((got - want).abs() <= tol * want + floor), f"request {r}"
+
+
+@pytest.mark.parametrize("Dh", [64, 128])
+@pytest.mark.parametrize("big", [1.0, 2.0 ** 118])
+def test_prefill_row_led_by_one_key(Dh, big):
+    """Rows whose largest logit lies 12 to 15.9 powers of two above a key of the
+    first 32 and far above all others, at a key further on: the largest
+    probability is exactly 1 and the sum of the others below 2^-11 of it (and
+    their values 0), so the output is that key's value, bit for bit (half a unit
+    in the last place of bf16 is at least 2^-10), and as finite as it."""
+    lead, P = [32, 40, 63, 64, 100, 129, 200], 260
+    R, Hq, Hkv = len(lead), 4, 4
+    gen = torch.Generator("cuda").manual_seed(Dh)
+    q = torch.zeros((1, R * P, Hq, Dh), device="cuda")
+    k = torch.zeros((1, R * P, Hkv, Dh), device="cuda")
+    v = (torch.randn((1, R * P, Hkv, Dh), device="cuda", generator=gen) * big).bfloat16()
+    q[..., 0] = 8.0
+    unit = np.sqrt(Dh) / (8.0 * np.log2(np.e))   # of k[..., 0]: one power of two of the probability
+    k[..., 0] = -60.0 * unit
+    for r, j in enumerate(lead):
+        k[0, r * P + 5, :, 0], v[0, r * P + 5] = 0.0, 0.0
+        for h in range(Hkv):
+            k[0, r * P + j, h, 0] = (12.2 + 0.9 * h + 0.13 * r) * unit
+    cu = (np.arange(R + 1) * P).astype(np.int32)
+    b = last.Batch.make(1, Hq, Hkv, Dh, cu, np.full(R, 8, np.int32), (np.arange(R + 1) * 240).astype(np.int32))
+    out, _ = last.prefill_attention(b, q.bfloat16(), k.bfloat16(), v)
+    for r, j in enumerate(lead):
+        a = r * P + j
+        bad = int((out[0, a:r * P + P] != v[0, a]).sum())
+        assert bad == 0, f"request {r}, key {j}: {bad} values differ"
