@@ -55,7 +55,6 @@
 // 256 to 16384 tokens (1536 wide), 1.52 against 1.01 for 32 x 2880 (4096).
 //   k_rfail    after a timeout, marks the unfinished requests invalid.
 #include <algorithm>
-#include <climits>
 #include <cstdlib>
 #include <math.h>
 
@@ -187,7 +186,7 @@ struct RArgs {
   unsigned long long *head;        // next task index
   uint32_t *live;                  // unfinished requests
   uint32_t *abort_word;            // set on a timeout or an impossible state
-  int R, Dv, max_rounds;
+  int R, Dv;
   int64_t Q;                       // tasks a round
   int64_t limit;                   // wall-clock ticks a wait may take
 };
@@ -1073,11 +1072,20 @@ __device__ __forceinline__ int64_t decode_task(int64_t u, int64_t R, Ft ft, int 
   return 0;
 }
 
+// Whether a task of round n whose dependencies are complete shows a fault: the
+// first round makes one pick and every later one at least one, so the select of
+// round K finds K picks and ends the request, and no task of a later round ever
+// has its dependencies. (How far the queue's head has run says nothing: blocks
+// pass over the tasks of finished requests without waiting, so beside one
+// unfinished request of c tasks a round the head runs up to grid / c rounds
+// ahead of it.)
+__device__ __forceinline__ bool past_last_round(int64_t n, int64_t K) { return n > K; }
+
 __global__ __launch_bounds__(kRThreads) void k_rounds(RArgs a) {
   __shared__ SmAll sm;
   __shared__ unsigned long long shk[kRWaves];
   __shared__ int shi[kRWaves];
-  __shared__ int s_task[4];   // status (0 run, 2 exit), request, kind, sub-index
+  __shared__ int s_task[5];   // status (0 run, 2 exit), request, kind, sub-index, round
   __shared__ int s_ft[kFtLds];   // fold-tile prefixes of batches of fewer than kFtLds requests
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = uni(tid >> 6);
@@ -1096,6 +1104,7 @@ __global__ __launch_bounds__(kRThreads) void k_rounds(RArgs a) {
       if (lane == 0 && prev >= 0)
         __hip_atomic_fetch_add(a.dcnt + prev, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       int status = 0, r = 0, kind = 0, sub = 0;
+      int64_t n = 0;
       do {
         unsigned long long qi = 0ull;
         if (lane == 0) qi = __hip_atomic_fetch_add(a.head, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1109,15 +1118,8 @@ __global__ __launch_bounds__(kRThreads) void k_rounds(RArgs a) {
         }
         const int64_t m = (int64_t)(qi / (unsigned long long)a.Q);   // macro-round
         const int64_t u = (int64_t)qi - m * a.Q;
-        if (m > a.max_rounds) {
-          // every request ends by round K_r, and a block runs at most two
-          // tasks ahead of the others: an index this far means a fault
-          if (lane == 0) st_u32(a.abort_word, 1u);
-          status = 2;
-          break;
-        }
         const int64_t tq = decode_task(u, a.R, ft_at, kind, r, sub);
-        const int64_t n = m + tq;   // tq = -1: B's folds of the previous round
+        n = m + tq;   // tq = -1: B's folds of the previous round
         if (n < 0) {
           status = 1;   // B's folds before its first round: no task
           continue;
@@ -1161,12 +1163,13 @@ __global__ __launch_bounds__(kRThreads) void k_rounds(RArgs a) {
         s_task[1] = r;
         s_task[2] = kind;
         s_task[3] = sub;
+        s_task[4] = (int)n;   // below 2^31: the counts reached it
       }
     }
     __syncthreads();
     const int status = uni(s_task[0]);
     if (status == 2) break;
-    const int r = uni(s_task[1]), kind = uni(s_task[2]), sub = uni(s_task[3]);
+    const int r = uni(s_task[1]), kind = uni(s_task[2]), sub = uni(s_task[3]), n = uni(s_task[4]);
     __syncthreads();
     Req q;
     q.r = r;
@@ -1174,6 +1177,10 @@ __global__ __launch_bounds__(kRThreads) void k_rounds(RArgs a) {
     q.N = uni(a.cu_vis[r + 1]) - (int)q.n0;
     q.k0 = uni(a.cu_keep[r]);
     q.K = uni(a.cu_keep[r + 1]) - (int)q.k0;
+    if (past_last_round(n, q.K)) {
+      if (tid == 0) st_u32(a.abort_word, 1u);
+      break;
+    }
     if (kind == 0)
       task_select(a, sm, q, shk, shi);
     else if (kind == 2)
@@ -1250,10 +1257,6 @@ hipError_t launch_round_pick(int32_t R, int32_t Dv, const SelectPlan &p, const S
   a.R = R;
   a.Dv = Dv;
   const int grid = std::max(1, device_cus());
-  // macro-rounds: at most K_max + 1 rounds per request, one more for the
-  // second half's last folds, plus those the blocks can be ahead of the last
-  // one (each holds one task and may take one more before it sees the end)
-  a.max_rounds = (int)std::min<int64_t>(INT_MAX / 2, p.K_max + 4 + (2 * (int64_t)grid + Q - 1) / Q);
   a.Q = Q;
   a.limit = device_wall_khz() * wait_us / 1000;
   launch_begin("rounds", s);

@@ -304,3 +304,21 @@ def test_default_form_depends_on_the_budgets(R, lo, hi, Dv):
         with pytest.raises(last.LastError) as e:
             last.diverse_select(w, feats, cv, ck, ws=ws[:-256])
         assert e.value.status == last.LAST_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("R,N,K,Dv", [(64, 1024, 16, 4096), (32, 2880, 10, 1024), (256, 256, 8, 256)])
+def test_rounds_one_slow_request(R, N, K, Dv):
+    """One request makes a pick a round (tokens along an arc under equal
+    relevance: a pick lowers every other candidate) while all others need one
+    round of picks. The blocks then pass over the finished requests' tasks far
+    ahead of it, which must not end the call."""
+    gen = torch.Generator("cuda").manual_seed(R)
+    feats = torch.randn((R * N, Dv), device="cuda", generator=gen)
+    w = torch.exp(2.0 * torch.randn(R * N, device="cuda", generator=gen))
+    a = N * (R // 2)
+    th = torch.arange(N, device="cuda") * (np.pi / 2 / N)
+    feats[a:a + N] = torch.cos(th)[:, None] * feats[a] + torch.sin(th)[:, None] * feats[a + 1]
+    w[a:a + N] = 1.0
+    cv, ck = (np.arange(R + 1) * N).astype(np.int32), (np.arange(R + 1) * K).astype(np.int32)
+    kept, _, _ = both(feats.bfloat16(), w, cv, ck, f"slow request {R} x {N}")
+    assert (kept >= 0).all()

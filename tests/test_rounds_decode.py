@@ -9,6 +9,11 @@ round's folds; candidates need the select; the greedy needs the candidates;
 the folds need the greedy) sit at smaller queue positions. This test
 compiles the function's own text with the host compiler and checks both on
 batches of several shapes.
+
+The queue itself is then run in a model on the host: blocks that take task
+indices in turn, wait for a task's dependencies and pass over the tasks of
+finished requests, with the task order and the fault check of the kernel's own
+text. A batch whose rounds all go well must end every request.
 """
 import os
 import re
@@ -119,3 +124,127 @@ def test_decode_order(decoder, N):
             deps = [(2, r, n, 0)]
         for dep in deps:
             assert dep in pos and pos[dep] < p, f"{(kind, r, n, s)} listed before its dependency {dep}"
+
+
+# The queue of k_rounds as a discrete-event model: BLOCKS blocks, each taking the
+# next index at a cost of DQ, a task of a finished request being passed over at
+# once; durations by kind; one round's picks of request r being per[r] at most.
+# Prints: requests finished, whether the fault check fired, the largest number
+# of macro-rounds the head ran past the oldest unfinished request's round.
+MODEL = r"""
+#include <algorithm>
+#include <cstdint>
+#include <cstdio>
+#include <queue>
+#include <vector>
+struct Wait { int block; int64_t need; int kind, sub; int64_t n; };
+int main() {
+  int R, BLOCKS; double DQ, dur[4];
+  if (scanf("%d %d %lf %lf %lf %lf %lf", &R, &BLOCKS, &DQ, dur, dur + 1, dur + 2, dur + 3) != 7) return 1;
+  std::vector<int64_t> ft(R + 1, 0), K(R), per(R), t(R, 0), done(R, 0), round(R, 0), np(R, 0);
+  for (int i = 0; i < R; ++i) {
+    long a, b, c;
+    if (scanf("%ld %ld %ld", &a, &b, &c) != 3) return 1;
+    ft[i + 1] = ft[i] + a; K[i] = b; per[i] = c;
+  }
+  auto fta = [&](int64_t i) -> int64_t { return ft[i]; };
+  int64_t Q = 0, head = 0, lead = 0; int live = R; bool abort_ = false;
+  for (int i = 0; i < R; ++i) Q += 2 + kCT + (ft[i + 1] - ft[i]);
+  std::vector<char> fin(R, 0);
+  std::vector<std::vector<Wait>> waits(R);
+  struct Ev { double at; int block, r, kind; int64_t n; };
+  auto later = [](const Ev &a, const Ev &b) { return a.at > b.at || (a.at == b.at && a.block > b.block); };
+  std::priority_queue<Ev, std::vector<Ev>, decltype(later)> ev(later);
+  for (int b = 0; b < BLOCKS; ++b) ev.push({0.0, b, -1, 0, 0});
+  auto start = [&](double at, int b, int r, int kind, int64_t n) {
+    if (past_last_round(n, K[r])) { abort_ = true; return; }
+    if (kind == 0) round[r] = n;
+    ev.push({at + dur[kind], b, r, kind, n});
+  };
+  long steps = 0;
+  while (!ev.empty() && !abort_ && ++steps < 50000000) {
+    Ev e = ev.top(); ev.pop();
+    if (e.r >= 0) {   // the task's effects, then its count
+      const int r = e.r;
+      if (e.kind == 0) {
+        if (e.n == 0) t[r] = 1; else if (t[r] >= K[r]) fin[r] = 1;
+        if (e.n == 0 && K[r] == 1) fin[r] = 1;
+        if (fin[r]) --live;
+      }
+      if (e.kind == 2 && e.n > 0) t[r] = std::min(K[r], t[r] + per[r]);
+      ++done[r];
+      for (size_t i = 0; i < waits[r].size();) {
+        const Wait w = waits[r][i];
+        if (!fin[r] && done[r] < w.need) { ++i; continue; }
+        waits[r].erase(waits[r].begin() + i);
+        if (fin[r]) ev.push({e.at + DQ, w.block, -1, 0, 0}); else start(e.at + 1.0, w.block, r, w.kind, w.n);
+      }
+      ev.push({e.at + DQ, e.block, -1, 0, 0});
+      continue;
+    }
+    if (live == 0) continue;   // the block ends
+    const int64_t q = head++, m = q / Q;
+    int64_t oldest = INT64_MAX;
+    for (int i = 0; i < R; ++i) if (!fin[i]) oldest = std::min(oldest, round[i]);
+    lead = std::max(lead, m - oldest);
+    int kind = 0, r = 0, sub = 0;
+    const int64_t n = m + decode_task(q - m * Q, (int64_t)R, fta, kind, r, sub);
+    if (n < 0 || fin[r]) { ev.push({e.at + DQ, e.block, -1, 0, 0}); continue; }
+    const int64_t c = 2 + kCT + ft[r + 1] - ft[r];
+    const int64_t need = n * c + (kind == 0 ? 0 : kind == 1 ? 1 : kind == 2 ? 1 + kCT : 2 + kCT);
+    if (done[r] >= need) start(e.at + 1.0, e.block, r, kind, n);
+    else waits[r].push_back({e.block, need, kind, sub, n});
+  }
+  printf("%d %d %ld\n", R - live, abort_ ? 1 : 0, (long)lead);
+  return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def model(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    src, hdr = open(SRC).read(), open(HDR).read()
+    fns = ""
+    for head in ("template <typename Ft>\n__device__ __forceinline__ int64_t decode_task",
+                 "__device__ __forceinline__ bool past_last_round"):
+        a = src.index(head)
+        eol = src.index("\n", a)
+        b = eol if src[eol - 1] == "}" else src.index("\n}\n", a) + 2   # a function on one line or several
+        fns += src[a:b].replace("__device__ __forceinline__ ", "") + "\n"
+    d = tmp_path_factory.mktemp("queue")
+    cpp, exe = d / "queue.cpp", d / "queue"
+    k_ct = _constant(hdr, "kRoundCandTasks")
+    cpp.write_text(f"#include <cstdint>\nstatic const int kCT = {k_ct};\n" + fns + MODEL)
+    subprocess.run([gxx, "-O2", "-std=c++17", "-o", str(exe), str(cpp)], check=True)
+    return str(exe), _constant(hdr, "kRoundFoldRows")
+
+
+@pytest.mark.parametrize("dq", [0.5, 2.5, 5.5])
+@pytest.mark.parametrize("R,N,K,slow", [
+    (64, 1024, 16, 1),     # one request whose rounds make one pick each
+    (32, 2880, 10, 1),
+    (64, 1024, 32, 2),
+    (128, 600, 24, 1),
+    (256, 256, 8, 1),
+    (8, 16384, 40, 1),
+    (1, 5000, 60, 1),
+    (33, 1500, 16, 33),    # every request slow
+])
+def test_queue_ends_every_request(model, R, N, K, slow, dq):
+    exe, f_rows = model
+    rng = np.random.default_rng(R + K)
+    reqs = []
+    for r in range(R):
+        n = int(rng.integers(max(1, N // 2), N + 1)) if N < 1000 else N
+        reqs.append(((n + f_rows - 1) // f_rows, 2 if K == 24 and r >= slow else K, 1 if r < slow else 128))
+    for order in (reqs, reqs[::-1]):
+        out = subprocess.run([exe], input=f"{R} 256 {dq} 23 20 89 70 " + " ".join("%d %d %d" % x for x in order),
+                             capture_output=True, text=True, check=True, timeout=60).stdout.split()
+        ended, aborted, lead = map(int, out)
+        assert (ended, aborted) == (R, 0)
+        if (R, N, K) == (64, 1024, 16) and order is reqs:
+            # far past K rounds: nothing may be concluded from the head's position
+            assert lead > K + 4, lead
