@@ -135,7 +135,6 @@ constexpr int kMcSlotWords = 256;    // exchange words per request of the multi-
 // takes (its select keys live in LDS).
 constexpr int kRoundCands = 192;
 constexpr int kRoundPicks = 128;
-constexpr int kRoundCandTasks = 0;    // candidate-Gram tasks of their own a round (the greedy task forms it)
 constexpr int kRoundFoldRows = 256;
 constexpr int kRoundMaxDv = 4096;
 constexpr int kRoundMaxN = 32768;

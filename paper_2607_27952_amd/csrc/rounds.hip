@@ -39,13 +39,12 @@
 //              request and round: S (select the candidates), G (the
 //              candidates' distances and the greedy on them), F (fold the
 //              picks into 256 tokens each), listed round by round and, within
-//              a round, phase by phase. (The task order also provides for C,
-//              kCT tasks between S and G; there are none.) A block takes the
-//              next task index from a global counter and waits until the
-//              tasks it depends on (all with smaller indices, so already taken
-//              by running blocks) have completed: no block ever waits for a
-//              block that has not started, so the grid needs no co-residency.
-//              Every wait is bounded by a wall-clock limit.
+//              a round, phase by phase. A block takes the next task index from
+//              a global counter and waits until the tasks it depends on (all
+//              with smaller indices, so already taken by running blocks) have
+//              completed: no block ever waits for a block that has not started,
+//              so the grid needs no co-residency. Every wait is bounded by a
+//              wall-clock limit.
 //
 // What bounds it: the folds, which read X once a round (video batch, 8 x
 // 16384 tokens of 3584: 10.6 rounds of 128 picks, 5440 folds of 89 us on 256
@@ -83,7 +82,6 @@ constexpr int kFTokInstr = kFTokPieces / 64 / kRWaves;  // LDS-DMA instructions 
 constexpr int kFTiles = kRP / 32;                       // 32-pick tiles of a fold task
 constexpr int kFPickInstr = kFPickPieces / 64 / kRWaves;   // ... picks, of a fold with every tile
 static_assert(kFTiles % 2 == 0 && kFPickInstr == kFTiles / 2, "a pick DMA instruction a wave per two tiles");
-constexpr int kCT = kRoundCandTasks;           // C tasks per request and round
 constexpr int kGRing = 6;                      // candidate-Gram ring stages (five in flight)
 constexpr int kGStagePieces = kRB * kFCols * 2 / 16;    // 16-byte pieces of candidates a stage
 constexpr int kGPerWave = kGStagePieces / 64 / kRWaves;  // LDS-DMA instructions a wave
@@ -985,16 +983,15 @@ __device__ void task_fold(const RArgs &a, SmAll &sm, const Req &q, int f) {
 // A = [0, RA) and B = [RA, R), half a round apart, so that one half's serial
 // chain (select, candidate Gram, greedy) runs while the other half folds.
 // Macro-round m lists, in this order:
-//   S of A's round m; the first half of B's folds of round m - 1; C (kCT
-//   each) of A's round m; G of A's round m; the rest of B's folds; S of B's
-//   round m; the first half of A's folds of round m; C and G of B's round m;
-//   the rest of A's folds.
-// The folds listed between a select and its candidate tasks keep the blocks
-// busy while the select runs. Each task depends only on tasks listed before
-// it. Sets kind (0 S, 1 C, 2 G, 3 F), the request and the sub-index (C: the
-// block pair; F: the fold tile within the request); returns -1 for B's folds
-// (they belong to round m - 1), else 0. `ft(i)` is the first fold tile of
-// request i (ft(R) the total). Every value is wave-uniform.
+//   S of A's round m; the first half of B's folds of round m - 1; G of A's
+//   round m; the rest of B's folds; S of B's round m; the first half of A's
+//   folds of round m; G of B's round m; the rest of A's folds.
+// The folds listed between a select and its greedy keep the blocks busy while
+// the select runs. Each task depends only on tasks listed before it. Sets kind
+// (0 S, 1 G, 2 F), the request and the sub-index (F: the fold tile within the
+// request); returns -1 for B's folds (they belong to round m - 1), else 0.
+// `ft(i)` is the first fold tile of request i (ft(R) the total). Every value
+// is wave-uniform.
 template <typename Ft>
 __device__ __forceinline__ int64_t decode_task(int64_t u, int64_t R, Ft ft, int &kind, int &r, int &sub) {
   const int64_t RA = (R + 1) / 2, RB = R - RA;
@@ -1010,7 +1007,7 @@ __device__ __forceinline__ int64_t decode_task(int64_t u, int64_t R, Ft ft, int 
       else
         hi = mid - 1;
     }
-    kind = 3;
+    kind = 2;
     r = (int)lo;
     sub = (int)(f - ft(lo));
   };
@@ -1026,15 +1023,8 @@ __device__ __forceinline__ int64_t decode_task(int64_t u, int64_t R, Ft ft, int 
     return -1;
   }
   x -= hB;
-  if (kCT > 0 && x < RA * kCT) {
-    kind = 1;
-    r = (int)(x / (kCT > 0 ? kCT : 1));
-    sub = (int)(x % (kCT > 0 ? kCT : 1));
-    return 0;
-  }
-  x -= RA * kCT;
   if (x < RA) {
-    kind = 2;
+    kind = 1;
     r = (int)x;
     return 0;
   }
@@ -1055,15 +1045,8 @@ __device__ __forceinline__ int64_t decode_task(int64_t u, int64_t R, Ft ft, int 
     return 0;
   }
   x -= hA;
-  if (kCT > 0 && x < RB * kCT) {
-    kind = 1;
-    r = (int)(RA + x / (kCT > 0 ? kCT : 1));
-    sub = (int)(x % (kCT > 0 ? kCT : 1));
-    return 0;
-  }
-  x -= RB * kCT;
   if (x < RB) {
-    kind = 2;
+    kind = 1;
     r = (int)(RA + x);
     return 0;
   }
@@ -1071,6 +1054,12 @@ __device__ __forceinline__ int64_t decode_task(int64_t u, int64_t R, Ft ft, int 
   fold(0, RA, hA + x);
   return 0;
 }
+
+// Tasks of a request of `tiles` fold tiles a round, and how many of its tasks are
+// complete before one of this kind may start in round n: every task of earlier
+// rounds and, in its own, S before G, and both before F.
+__device__ __forceinline__ int64_t tasks_a_round(int64_t tiles) { return 2 + tiles; }
+__device__ __forceinline__ int64_t tasks_before(int64_t n, int kind, int64_t tiles) { return n * tasks_a_round(tiles) + kind; }
 
 // Whether a task of round n whose dependencies are complete shows a fault: the
 // first round makes one pick and every later one at least one, so the select of
@@ -1124,9 +1113,7 @@ __global__ __launch_bounds__(kRThreads) void k_rounds(RArgs a) {
           status = 1;   // B's folds before its first round: no task
           continue;
         }
-        const int64_t tiles = ft_at(r + 1) - ft_at(r);
-        const int64_t c = 2 + kCT + tiles;
-        const int64_t need = n * c + (kind == 0 ? 0 : kind == 1 ? 1 : kind == 2 ? 1 + kCT : 2 + kCT);
+        const int64_t need = tasks_before(n, kind, ft_at(r + 1) - ft_at(r));
         const uint64_t t0 = wall_clock64();
         for (;;) {
           uint32_t done = ld_u32(a.dcnt + r);
@@ -1143,7 +1130,7 @@ __global__ __launch_bounds__(kRThreads) void k_rounds(RArgs a) {
             // The loads above may be served out of order: read the end mark
             // again now that the counts are there. A fold needs no second
             // look (it returns when the picks are complete).
-            if (kind != 3 && uni(ld_i32(a.st + 4 * r + kStFin)) != 0) status = 1;
+            if (kind != 2 && uni(ld_i32(a.st + 4 * r + kStFin)) != 0) status = 1;
             break;
           }
           if (ab != 0u) {
@@ -1183,7 +1170,7 @@ __global__ __launch_bounds__(kRThreads) void k_rounds(RArgs a) {
     }
     if (kind == 0)
       task_select(a, sm, q, shk, shi);
-    else if (kind == 2)
+    else if (kind == 1)
       task_greedy(a, sm, q);
     else
       task_fold(a, sm, q, sub);

@@ -1,14 +1,14 @@
 """The task order of the k-center in rounds, checked on the host.
 
-`decode_task` in rounds.hip maps a queue position to a task (select,
-candidate block pair, greedy, or fold tile of one request and round). The
-persistent kernel is deadlock-free and its completion counts are exact only
-if, in every macro-round, each task of each request appears exactly once
-and each task's dependencies (Sec. 3.4: a round's select needs the previous
-round's folds; candidates need the select; the greedy needs the candidates;
-the folds need the greedy) sit at smaller queue positions. This test
-compiles the function's own text with the host compiler and checks both on
-batches of several shapes.
+`decode_task` in rounds.hip maps a queue position to a task (select, greedy or
+fold tile of one request and round) and `tasks_before` says how many of the
+request's tasks must be complete for it. The persistent kernel is deadlock-free
+and its completion counts are exact only if, in every macro-round, each task of
+each request appears exactly once, each task's dependencies (Sec. 3.4: a
+round's select needs the previous round's folds; the greedy needs the select;
+the folds need the greedy) sit at smaller queue positions, and the count is
+that of the dependencies. This test compiles the functions' own text with the
+host compiler and checks all three on batches of several shapes.
 
 The queue itself is then run in a model on the host: blocks that take task
 indices in turn, wait for a task's dependencies and pass over the tasks of
@@ -34,22 +34,35 @@ def _constant(text, name):
     return int(m.group(1))
 
 
-@pytest.fixture(scope="module")
-def decoder(tmp_path_factory):
+def _functions():
+    """The text of the queue's functions, for the host compiler."""
+    src, fns = open(SRC).read(), "#include <cstdint>\n"
+    for head in ("template <typename Ft>\n__device__ __forceinline__ int64_t decode_task",
+                 "__device__ __forceinline__ int64_t tasks_a_round", "__device__ __forceinline__ int64_t tasks_before",
+                 "__device__ __forceinline__ bool past_last_round"):
+        a = src.index(head)
+        eol = src.index("\n", a)
+        b = eol if src[eol - 1] == "}" else src.index("\n}\n", a) + 2   # a function on one line or several
+        fns += src[a:b].replace("__device__ __forceinline__ ", "") + "\n"
+    return fns
+
+
+def _compile(tmp_path_factory, name, text):
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("no host C++ compiler")
-    src = open(SRC).read()
-    hdr = open(HDR).read()
-    sub = _constant(hdr, "kRoundCands") // 32
-    k_ct = sub * (sub + 1) // 2   # 32 x 32 block pairs of the candidate Gram, one task each
-    f_rows = _constant(hdr, "kRoundFoldRows")
-    a = src.index("template <typename Ft>\n__device__ __forceinline__ int64_t decode_task")
-    b = src.index("\n}\n", a) + 3
-    fn = src[a:b].replace("__device__ __forceinline__ ", "")
-    prog = (
-        "#include <cstdint>\n#include <cstdio>\n#include <vector>\n"
-        f"static const int kCT = {k_ct};\n" + fn + r"""
+    d = tmp_path_factory.mktemp(name)
+    cpp, exe = d / f"{name}.cpp", d / name
+    cpp.write_text(_functions() + text)
+    subprocess.run([gxx, "-O2", "-std=c++17", "-o", str(exe), str(cpp)], check=True)
+    return str(exe), _constant(open(HDR).read(), "kRoundFoldRows")
+
+
+@pytest.fixture(scope="module")
+def decoder(tmp_path_factory):
+    return _compile(tmp_path_factory, "decode", r"""
+#include <cstdio>
+#include <vector>
 int main() {
   int R, M;
   if (scanf("%d %d", &R, &M) != 2) return 1;
@@ -57,21 +70,17 @@ int main() {
   for (int i = 0; i < R; ++i) { long t; if (scanf("%ld", &t) != 1) return 1; ft[i + 1] = ft[i] + t; }
   auto fta = [&](int64_t i) -> int64_t { return ft[i]; };
   int64_t Q = 0;
-  for (int i = 0; i < R; ++i) Q += 2 + kCT + (ft[i + 1] - ft[i]);
+  for (int i = 0; i < R; ++i) Q += tasks_a_round(ft[i + 1] - ft[i]);
   for (int64_t m = 0; m < M; ++m)
     for (int64_t u = 0; u < Q; ++u) {
       int kind = 0, r = 0, sub = 0;
-      const int64_t tq = decode_task(u, (int64_t)R, fta, kind, r, sub);
-      printf("%ld %ld %d %d %ld %d\n", (long)m, (long)u, kind, r, (long)(m + tq), sub);
+      const int64_t n = m + decode_task(u, (int64_t)R, fta, kind, r, sub);
+      printf("%ld %ld %d %d %ld %d %ld\n", (long)m, (long)u, kind, r, (long)n, sub,
+             (long)tasks_before(n, kind, ft[r + 1] - ft[r]));
     }
   return 0;
 }
 """)
-    d = tmp_path_factory.mktemp("decode")
-    cpp, exe = d / "decode.cpp", d / "decode"
-    cpp.write_text(prog)
-    subprocess.run([gxx, "-O1", "-std=c++17", "-o", str(exe), str(cpp)], check=True)
-    return str(exe), k_ct, f_rows
 
 
 CASES = [
@@ -86,7 +95,7 @@ CASES = [
 
 @pytest.mark.parametrize("N", CASES + ["ragged128", "ragged33"], ids=str)
 def test_decode_order(decoder, N):
-    exe, k_ct, f_rows = decoder
+    exe, f_rows = decoder
     rng = np.random.default_rng(7)
     if N == "ragged128":
         N = list(rng.integers(256, 16385, 128))
@@ -97,33 +106,33 @@ def test_decode_order(decoder, N):
     out = subprocess.run([exe], input=f"{R} {M} " + " ".join(map(str, tiles)), capture_output=True, text=True,
                          check=True).stdout
     rows = np.array([list(map(int, line.split())) for line in out.split("\n") if line], np.int64)
-    Q = sum(2 + k_ct + t for t in tiles)
+    Q = sum(2 + t for t in tiles)
     assert len(rows) == M * Q
     RA = (R + 1) // 2
     pos = {}
     for m in range(M):
-        got = [tuple(x) for x in rows[rows[:, 0] == m][:, 2:]]
+        got = [tuple(x) for x in rows[rows[:, 0] == m][:, 2:6]]
         assert len(set(got)) == Q, "a task listed twice in one macro-round"
         want = set()
         for r in range(R):
-            for kind, count in ((0, 1), (1, k_ct), (2, 1), (3, tiles[r])):
-                n = m - 1 if (kind == 3 and r >= RA) else m   # the second half folds a round behind
+            for kind, count in ((0, 1), (1, 1), (2, tiles[r])):
+                n = m - 1 if (kind == 2 and r >= RA) else m   # the second half folds a round behind
                 want.update((kind, r, n, s) for s in range(count))
         assert set(got) == want
         for u, key in enumerate(got):
             if key[2] >= 0:
                 pos[key] = m * Q + u
+    need = {tuple(x[2:6]): x[6] for x in rows}
     for (kind, r, n, s), p in pos.items():
+        # every task of the request that must come first: all of round n - 1, and
+        # in round n the select before the greedy and both before the folds
         if kind == 0:
-            deps = [(3, r, n - 1, t) for t in range(tiles[r])] if n > 0 else []
-        elif kind == 1:
-            deps = [(0, r, n, 0)]
-        elif kind == 2:
-            deps = [(1, r, n, t) for t in range(k_ct)]
+            deps = [(2, r, n - 1, t) for t in range(tiles[r])] or [(1, r, n - 1, 0)] if n > 0 else []
         else:
-            deps = [(2, r, n, 0)]
+            deps = [(kind - 1, r, n, 0)]
         for dep in deps:
             assert dep in pos and pos[dep] < p, f"{(kind, r, n, s)} listed before its dependency {dep}"
+        assert need[kind, r, n, s] == n * (2 + tiles[r]) + kind
 
 
 # The queue of k_rounds as a discrete-event model: BLOCKS blocks, each taking the
@@ -133,14 +142,13 @@ def test_decode_order(decoder, N):
 # of macro-rounds the head ran past the oldest unfinished request's round.
 MODEL = r"""
 #include <algorithm>
-#include <cstdint>
 #include <cstdio>
 #include <queue>
 #include <vector>
 struct Wait { int block; int64_t need; int kind, sub; int64_t n; };
 int main() {
-  int R, BLOCKS; double DQ, dur[4];
-  if (scanf("%d %d %lf %lf %lf %lf %lf", &R, &BLOCKS, &DQ, dur, dur + 1, dur + 2, dur + 3) != 7) return 1;
+  int R, BLOCKS; double DQ, dur[3];
+  if (scanf("%d %d %lf %lf %lf %lf", &R, &BLOCKS, &DQ, dur, dur + 1, dur + 2) != 6) return 1;
   std::vector<int64_t> ft(R + 1, 0), K(R), per(R), t(R, 0), done(R, 0), round(R, 0), np(R, 0);
   for (int i = 0; i < R; ++i) {
     long a, b, c;
@@ -149,7 +157,7 @@ int main() {
   }
   auto fta = [&](int64_t i) -> int64_t { return ft[i]; };
   int64_t Q = 0, head = 0, lead = 0; int live = R; bool abort_ = false;
-  for (int i = 0; i < R; ++i) Q += 2 + kCT + (ft[i + 1] - ft[i]);
+  for (int i = 0; i < R; ++i) Q += tasks_a_round(ft[i + 1] - ft[i]);
   std::vector<char> fin(R, 0);
   std::vector<std::vector<Wait>> waits(R);
   struct Ev { double at; int block, r, kind; int64_t n; };
@@ -171,7 +179,7 @@ int main() {
         if (e.n == 0 && K[r] == 1) fin[r] = 1;
         if (fin[r]) --live;
       }
-      if (e.kind == 2 && e.n > 0) t[r] = std::min(K[r], t[r] + per[r]);
+      if (e.kind == 1 && e.n > 0) t[r] = std::min(K[r], t[r] + per[r]);
       ++done[r];
       for (size_t i = 0; i < waits[r].size();) {
         const Wait w = waits[r][i];
@@ -190,8 +198,7 @@ int main() {
     int kind = 0, r = 0, sub = 0;
     const int64_t n = m + decode_task(q - m * Q, (int64_t)R, fta, kind, r, sub);
     if (n < 0 || fin[r]) { ev.push({e.at + DQ, e.block, -1, 0, 0}); continue; }
-    const int64_t c = 2 + kCT + ft[r + 1] - ft[r];
-    const int64_t need = n * c + (kind == 0 ? 0 : kind == 1 ? 1 : kind == 2 ? 1 + kCT : 2 + kCT);
+    const int64_t need = tasks_before(n, kind, ft[r + 1] - ft[r]);
     if (done[r] >= need) start(e.at + 1.0, e.block, r, kind, n);
     else waits[r].push_back({e.block, need, kind, sub, n});
   }
@@ -203,23 +210,7 @@ int main() {
 
 @pytest.fixture(scope="module")
 def model(tmp_path_factory):
-    gxx = shutil.which("g++")
-    if gxx is None:
-        pytest.skip("no host C++ compiler")
-    src, hdr = open(SRC).read(), open(HDR).read()
-    fns = ""
-    for head in ("template <typename Ft>\n__device__ __forceinline__ int64_t decode_task",
-                 "__device__ __forceinline__ bool past_last_round"):
-        a = src.index(head)
-        eol = src.index("\n", a)
-        b = eol if src[eol - 1] == "}" else src.index("\n}\n", a) + 2   # a function on one line or several
-        fns += src[a:b].replace("__device__ __forceinline__ ", "") + "\n"
-    d = tmp_path_factory.mktemp("queue")
-    cpp, exe = d / "queue.cpp", d / "queue"
-    k_ct = _constant(hdr, "kRoundCandTasks")
-    cpp.write_text(f"#include <cstdint>\nstatic const int kCT = {k_ct};\n" + fns + MODEL)
-    subprocess.run([gxx, "-O2", "-std=c++17", "-o", str(exe), str(cpp)], check=True)
-    return str(exe), _constant(hdr, "kRoundFoldRows")
+    return _compile(tmp_path_factory, "queue", MODEL)
 
 
 @pytest.mark.parametrize("dq", [0.5, 2.5, 5.5])
@@ -241,7 +232,7 @@ def test_queue_ends_every_request(model, R, N, K, slow, dq):
         n = int(rng.integers(max(1, N // 2), N + 1)) if N < 1000 else N
         reqs.append(((n + f_rows - 1) // f_rows, 2 if K == 24 and r >= slow else K, 1 if r < slow else 128))
     for order in (reqs, reqs[::-1]):
-        out = subprocess.run([exe], input=f"{R} 256 {dq} 23 20 89 70 " + " ".join("%d %d %d" % x for x in order),
+        out = subprocess.run([exe], input=f"{R} 256 {dq} 23 89 70 " + " ".join("%d %d %d" % x for x in order),
                              capture_output=True, text=True, check=True, timeout=60).stdout.split()
         ended, aborted, lead = map(int, out)
         assert (ended, aborted) == (R, 0)
