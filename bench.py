@@ -237,7 +237,23 @@ def stage_work(wl, row_pos=None):
 
 
 SCORE_KERNELS = ("score_prefix", "score_stream", "score_partial", "score_merge", "score_finalize")
-SIMILARITY_KERNELS = ("select_plan", "gram_diag", "gram", "norms", "rounds")
+SIMILARITY_KERNELS = ("select_plan", "gram_diag", "gram", "rounds_prep", "norms", "rounds")
+# the k-center's kernels by form; where the device chooses the form by the
+# relevance, the kernels of both are launched and those of one return at once
+FORM_KERNELS = {"matrix": ("gram_diag", "gram", "greedy"), "rounds": ("norms", "rounds")}
+
+
+def kcenter_form(kernels):
+    """Which form of the k-center ran: the rounds (no N x N matrix) or the matrix."""
+    ms = {f: sum(kernels[k].get("ms_per_step", 0.0) for k in ks if k in kernels) for f, ks in FORM_KERNELS.items()}
+    there = [f for f, key in (("rounds", ("rounds",)), ("matrix", ("gram", "gram_diag"))) if any(k in kernels for k in key)]
+    return max(there, key=lambda f: ms[f]) if there else None
+
+
+def form_not_taken(kernels):
+    """The kernels of the other form, which did nothing."""
+    form = kcenter_form(kernels)
+    return [k for f, ks in FORM_KERNELS.items() if form and f != form for k in ks if k in kernels]
 
 
 def similarity_summary(wl, kernels):
@@ -247,7 +263,7 @@ def similarity_summary(wl, kernels):
     rounds, which also run the greedy) is reported against the paper's work."""
     sw = stage_work(wl)
     rounds_ms = sum(kernels[k]["ms_per_step"] for k in ("norms", "rounds") if k in kernels)
-    if "rounds" in kernels and rounds_ms > 0:
+    if kcenter_form(kernels) == "rounds" and rounds_ms > 0:
         return {"form": "rounds", "paper_flops": sw["similarity_flops"],
                 "rounds_ms_per_step": round(rounds_ms, 4),
                 "tflops_on_paper_work": round(sw["similarity_flops"] / (rounds_ms * 1e-3) / 1e12, 2)}
@@ -506,7 +522,8 @@ def measure(args, name, budget, steps, warmup, source="last", prefill=False, con
     # work figures are per step; a kernel launched several times a step (the Gram
     # of a ragged batch, in groups) does its share per launch
     rooflines = [roofline_entry(k, bd, w / max(1.0, kernels[k]["launches"] / steps), kernels[k]["avg_ms"])
-                 for k, (bd, w) in work.items() if k in kernels and kernels[k]["avg_ms"] > 0]
+                 for k, (bd, w) in work.items()
+                 if k in kernels and kernels[k]["avg_ms"] > 0 and k not in form_not_taken(kernels)]
     # greedies launched on the library's side streams overlap the Gram; they are
     # reported but neither counted in the stage sums nor taken as the dominant kernel
     dominant = max((kv for kv in kernels.items() if kv[0] != "greedy_side"), key=lambda kv: kv[1]["ms_per_step"])[0]
@@ -547,7 +564,7 @@ def measure(args, name, budget, steps, warmup, source="last", prefill=False, con
         stage_roof["similarity"] = e
     if gather_ms > 0:
         stage_roof["gather"] = roofline_entry("gather", *sw["gather"], gather_ms)
-    if "greedy" in kernels and "greedy_side" not in kernels:
+    if "greedy" in kernels and "greedy_side" not in kernels and "greedy" not in form_not_taken(kernels):
         kk = np.diff(wl.cu_keep)
         stage_roof["greedy"] = {"bound": "latency", "steps_longest_request": int(kk.max()),
                                 "us_per_step_longest_request": round(kernels["greedy"]["ms_per_step"] * 1e3 / int(kk.max()), 3)}
@@ -578,11 +595,6 @@ def measure(args, name, budget, steps, warmup, source="last", prefill=False, con
 # batches, and the LLaVA-1.5 batch at its other two budgets): name, budget, steps.
 CONFIG_RUNS = (("c1_single_fp32", None, 50), ("c2_llava15", 128, 30), ("c2_llava15", 192, 30),
                ("c3_llava_next", None, 20), ("c4_dynres", None, 10), ("c5_video", None, 10))
-
-
-def kcenter_form(kernels):
-    """Which form of the k-center ran: the rounds (no N x N matrix) or the matrix."""
-    return "rounds" if "rounds" in kernels else "matrix" if "gram" in kernels or "gram_diag" in kernels else None
 
 
 def config_summary(m, budget):

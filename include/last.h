@@ -244,9 +244,10 @@ size_t diverse_select_workspace(int32_t R, const int32_t *cu_vis_h, int32_t Dv,
  *              By default the rounds take batches whose every request has
  *              8192 tokens or more and the shapes above, and other batches
  *              of those shapes where an estimate from the sizes and budgets
- *              says they are faster (the workspace is then still the
- *              matrix's, as the query, which knows no budgets, says); the
- *              environment
+ *              says they are faster, whatever the relevance or, with the
+ *              choice made on the device, unless a request's relevance is
+ *              even (the workspace is then still the matrix's, as the query,
+ *              which knows no budgets, says); the environment
  *              variable LAST_KCENTER_FORM=gram or =rounds forces one (rounds
  *              only where those shapes allow). The rounds run as a queue of
  *              tasks on one block per compute unit in which no block waits

@@ -232,11 +232,15 @@ __global__ __launch_bounds__(256) void k_tile_fill(const int32_t *__restrict__ c
 // lists in one launch, one block a request. A block sums the counts of the
 // requests before it (and of all of them, for the totals) itself, in a fixed
 // order, instead of reading k_select_plan's prefixes.
-__global__ __launch_bounds__(256) void k_plan_fill(const int32_t *__restrict__ cu_vis, int64_t diag_cap,
+// BY: the form was chosen on the device (nothing to do where it is the rounds).
+template <bool BY>
+__global__ __launch_bounds__(256) void k_plan_fill(const int32_t *__restrict__ cu_vis,
+                                                   const uint32_t *__restrict__ form, int64_t diag_cap,
                                                    int64_t off_cap, int32_t *__restrict__ dtile_off,
                                                    int32_t *__restrict__ otile_off, int64_t *__restrict__ d_off,
                                                    TileMeta *__restrict__ dtile, TileMeta *__restrict__ otile) {
   __shared__ int64_t sh[4][4];
+  if (BY && *form == 0u) return;
   const int r = blockIdx.x, R = gridDim.x;
   int64_t v[4] = {0, 0, 0, 0};   // diagonal, off-diagonal and matrix elements before r; diagonal in all
   for (int q = threadIdx.x; q < R; q += 256) {
@@ -522,8 +526,10 @@ inline int64_t persistent_grid(int64_t tiles, int cus) {
 
 template <bool DIAG>
 __global__ __launch_bounds__(kGramThreads) void k_gram_bf16(
-    const uint16_t *__restrict__ X, const TileMeta *__restrict__ meta, double *__restrict__ nn,
-    double *__restrict__ inv, int Dv, int64_t tiles, int64_t d_cap, float *__restrict__ dmat) {
+    const uint16_t *__restrict__ X, const TileMeta *__restrict__ meta, const uint32_t *__restrict__ form,
+    double *__restrict__ nn, double *__restrict__ inv, int Dv, int64_t tiles, int64_t d_cap,
+    float *__restrict__ dmat) {
+  if (form && *form == 0u) return;
   constexpr int kOps = DIAG ? 1 : 2;
   constexpr int kRing = DIAG ? kRingDiag : kRingOff;
   constexpr int kInstr = kOps * kDmaInstr;                  // per stage, all operands
@@ -1221,7 +1227,7 @@ hipError_t launch_gram_plan(int32_t R, const SelectPlan &p, const SelectWs &w, c
                             hipStream_t s) {
   launch_begin("select_plan", s);
   if (!p.ranked) {
-    hipLaunchKernelGGL(k_plan_fill, dim3(R), dim3(256), 0, s, cu_vis, p.tiles_diag, p.tiles_off, w.dtile_off,
+    hipLaunchKernelGGL(w.form ? k_plan_fill<true> : k_plan_fill<false>, dim3(R), dim3(256), 0, s, cu_vis, w.form, p.tiles_diag, p.tiles_off, w.dtile_off,
                        w.otile_off, w.d_off, w.dtile, w.otile);
     return launch_end(s);
   }
@@ -1238,7 +1244,7 @@ hipError_t launch_gram_diag(int32_t Dv, const SelectPlan &p, const SelectWs &w, 
                             hipStream_t s) {
   launch_begin("gram_diag", s);
   hipLaunchKernelGGL(k_gram_bf16<true>, dim3((unsigned)persistent_grid(p.tiles_diag, cus)), dim3(kGramThreads), 0,
-                     s, (const uint16_t *)feats, w.dtile, w.nn, w.inv, Dv, p.tiles_diag, p.d_elems, w.dmat);
+                     s, (const uint16_t *)feats, w.dtile, w.form, w.nn, w.inv, Dv, p.tiles_diag, p.d_elems, w.dmat);
   return launch_end(s);
 }
 
@@ -1247,7 +1253,7 @@ hipError_t launch_gram_off(int32_t Dv, const SelectPlan &p, const SelectWs &w, c
   if (nt <= 0) return hipSuccess;
   launch_begin("gram", s);
   hipLaunchKernelGGL(k_gram_bf16<false>, dim3((unsigned)persistent_grid(nt, cus)), dim3(kGramThreads), 0, s,
-                     (const uint16_t *)feats, w.otile + t0, w.nn, w.inv, Dv, nt, p.d_elems, w.dmat);
+                     (const uint16_t *)feats, w.otile + t0, w.form, w.nn, w.inv, Dv, nt, p.d_elems, w.dmat);
   return launch_end(s);
 }
 
@@ -1262,7 +1268,7 @@ hipError_t launch_similarity(int32_t R, int32_t Dv, last_dtype fdtype, const Sel
   // Measured, 128 x 128 tiles / sub-tiles in us, 4096 wide: 36 x 16 blocks
   // (one request of 1024 tokens) 69 / 61, 45 x 16 (three of 576) 72 / 62, 60 x
   // 16 (four of 576) 73 / 82; 15 x 16 (one of 576) 60 / 22, at 1536 36 / 12.
-  const bool pairs = fdtype == LAST_BF16 && Dv % 256 == 0 && Dv <= 128 * kPairMaxChunks &&
+  const bool pairs = !w.form && fdtype == LAST_BF16 && Dv % 256 == 0 && Dv <= 128 * kPairMaxChunks &&
                      (p.tiles_diag + p.tiles_off) * kSubs <= 3 * (int64_t)device_cus();
   if (pairs) {
     launch_begin("gram", s);
@@ -1276,12 +1282,13 @@ hipError_t launch_similarity(int32_t R, int32_t Dv, last_dtype fdtype, const Sel
       const int cus = device_cus();
       launch_begin("gram_diag", s);
       hipLaunchKernelGGL(k_gram_bf16<true>, dim3((unsigned)persistent_grid(p.tiles_diag, cus)), dim3(kGramThreads),
-                         0, s, (const uint16_t *)feats, w.dtile, w.nn, w.inv, Dv, p.tiles_diag, p.d_elems, w.dmat);
+                         0, s, (const uint16_t *)feats, w.dtile, w.form, w.nn, w.inv, Dv, p.tiles_diag, p.d_elems,
+                         w.dmat);
       if ((e = launch_end(s)) != hipSuccess) return e;
       if (p.tiles_off > 0) {
         launch_begin("gram", s);
         hipLaunchKernelGGL(k_gram_bf16<false>, dim3((unsigned)persistent_grid(p.tiles_off, cus)),
-                           dim3(kGramThreads), 0, s, (const uint16_t *)feats, w.otile, w.nn, w.inv, Dv,
+                           dim3(kGramThreads), 0, s, (const uint16_t *)feats, w.otile, w.form, w.nn, w.inv, Dv,
                            p.tiles_off, p.d_elems, w.dmat);
         if ((e = launch_end(s)) != hipSuccess) return e;
       }

@@ -190,6 +190,7 @@ struct SelectPlan {
   int32_t group_slices[kMaxGroups];
   bool rounds;             // the k-center in rounds (rounds.hip) instead of the matrix
   bool rounds_by_budget;   // ... by the estimate: the workspace is still the matrix form's
+  bool by_relevance;       // the form is chosen on the device (launch_by_relevance); a plain matrix plan
   int64_t round_Q;         // tasks a round of the rounds kernel
 };
 
@@ -202,6 +203,10 @@ struct SelectWs {
   float *dmat;                     // coverage distances, tile-major per request (cov_index)
   int32_t *req_order;              // [R] the request of each rank (ranked plans)
   unsigned long long *mc_slots;    // [R][kMcSlotWords] exchange words of the multi-block greedy, by rank
+  void *base;                      // the workspace
+  // a form chosen on the device: its word (0 rounds, 1 matrix), and [R] whether a
+  // request's relevance is too even; null where the host chose
+  uint32_t *form, *even;
   // the rounds form (nn and inv as above; nothing else of the matrix form)
   float *r_dl;                     // [N_total] running minimum coverage distance
   int32_t *r_cand, *r_picks;       // [R][kRoundCands], [R][kRoundPicks]
@@ -223,9 +228,10 @@ enum RoundsRule { kRoundsNever = 0, kRoundsByShape = 1, kRoundsAny = 2 };
 SelectPlan make_select_plan(int32_t R, const int32_t *cu_vis_h, const int32_t *cu_keep_h,
                             last_sel_mode mode, int32_t Dv, last_dtype fdtype, bool allow_groups,
                             RoundsRule rounds);
-// The rounds form: the shapes it takes, the norms (the first half, features
-// only), and the rounds themselves.
+// The rounds form: the shapes it takes, the state (and, with w.form set, the
+// choice of the form), the norms, and the rounds themselves.
 bool rounds_supported(int32_t N_max, int32_t Dv, last_dtype fdtype);
+hipError_t launch_round_prep(int32_t R, const SelectWs &w, const float *scores, const int32_t *cu_vis, hipStream_t s);
 hipError_t launch_round_norms(int32_t Dv, const SelectPlan &p, const SelectWs &w, const void *feats,
                               hipStream_t s);
 hipError_t launch_round_pick(int32_t R, int32_t Dv, const SelectPlan &p, const SelectWs &w, const float *scores,

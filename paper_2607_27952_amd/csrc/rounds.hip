@@ -34,7 +34,9 @@
 //
 // Kernels:
 //   k_rnorm    |x_i|^2 and 1 / |x_i| of every token (one pass over X).
-//   k_rprep    fold-tile prefixes and the per-request state.
+//   k_reven    (where the form is chosen on the device) whether a request's
+//              relevance is too even for the rounds.
+//   k_rprep    fold-tile prefixes, the per-request state and that choice.
 //   k_rounds   the rounds, as a queue of tasks on a persistent grid; per
 //              request and round: S (select the candidates), G (the
 //              candidates' distances and the greedy on them), F (fold the
@@ -181,6 +183,7 @@ struct RArgs {
   uint32_t *dcnt;                  // [R] completed tasks
   const int64_t *ftoff;            // [R + 1] fold-tile prefixes
   const unsigned long long *ctl;   // live (low word) and abort (high word), read together
+  const uint32_t *form;            // null, or the form chosen on the device
   unsigned long long *head;        // next task index
   uint32_t *live;                  // unfinished requests
   uint32_t *abort_word;            // set on a timeout or an impossible state
@@ -286,7 +289,9 @@ static_assert(kRoundMaxN <= 64 * kRThreads, "ordered_scan: one 64-bit mask a thr
 // themselves, in the Gram's 128-column chunks; 1 / |x_i| in fp64 (0 for a
 // zero row). One wave per 32 rows; two chunks of loads in flight.
 __global__ __launch_bounds__(256) void k_rnorm(const uint16_t *__restrict__ X, int64_t N_total, int Dv,
-                                               double *__restrict__ nn, double *__restrict__ inv) {
+                                               const uint32_t *__restrict__ form, double *__restrict__ nn,
+                                               double *__restrict__ inv) {
+  if (form && *form != 0u) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * 32;
   if (row0 >= N_total) return;
@@ -328,21 +333,104 @@ __global__ __launch_bounds__(256) void k_rnorm(const uint16_t *__restrict__ X, i
 }
 
 // ------------------------------------------------------------------- prep
+// even[r] = whether request r's relevance is too even for the rounds: its
+// N/16-th largest value within kEvenBins bins of its median, a bin being 1/32
+// of an octave (2 to 3%). The objectives of even relevance fall below the
+// bound after few picks of a round, whatever the features. (A request of at
+// most kRB tokens is its own candidates: no bound, so never too even.) Values
+// are binned by their float bits relative to the mean's. One block a request,
+// bound by the latency of its two passes over the relevance. Measured with
+// log-normal relevance of spread s (gap in bins; select call, matrix / rounds
+// in us), 32 x 2880 tokens 4096 wide, 1/9 kept: s 0.001 (0) 2027 / 2155, 0.1
+// (5) 1938 / 1266, 0.3 (14) 1960 / 1177; 64 x 1024 tokens, 1/16 kept: 0.03 (2)
+// 585 / 662, 0.1 (5) 569 / 573, 0.2 (10) 556 / 416.
+constexpr int kEvenThreads = 1024, kEvenBins = 8;
+__global__ __launch_bounds__(kEvenThreads) void k_reven(const float *__restrict__ scores,
+                                                        const int32_t *__restrict__ cu_vis,
+                                                        uint32_t *__restrict__ even) {
+  constexpr int kWaves = kEvenThreads / 64;
+  __shared__ uint32_t hist[kWaves][257];   // per-wave counts (padded: waves on different banks)
+  __shared__ uint32_t tot[256];
+  __shared__ float sh[kWaves];
+  const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t n0 = cu_vis[r];
+  const int N = cu_vis[r + 1] - (int)n0;
+  if (N <= kRB) {
+    if (tid == 0) even[r] = 0u;
+    return;
+  }
+  float sum = 0.f;
+  for (int i = tid; i < N; i += kEvenThreads) sum += clean_score(scores[n0 + i]);
+  for (int x = tid; x < kWaves * 257; x += kEvenThreads) (&hist[0][0])[x] = 0u;
+  sum = wave_sum(sum);
+  if (lane == 0) sh[wave] = sum;
+  __syncthreads();
+  float mean = 0.f;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) mean += sh[w];
+  const int mid = (int)__float_as_uint(mean / (float)N);
+  for (int i = tid; i < N; i += kEvenThreads) {
+    const int b = ((int)__float_as_uint(clean_score(scores[n0 + i])) - mid) >> 18;
+    atomicAdd(&hist[wave][min(max(b, -128), 127) + 128], 1u);
+  }
+  __syncthreads();
+  if (tid < 256) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) c += hist[w][tid];
+    tot[tid] = c;
+  }
+  __syncthreads();
+  if (tid >= 64) return;
+  // lane l holds bins 4 l .. 4 l + 3: the highest bin with at least `want`
+  // values in it and above
+  uint32_t above = 0;   // values in the bins of later lanes
+  for (int x = 0; x < 4; ++x) above += tot[4 * lane + x];
+  const uint32_t mine = above;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_down(above, o);
+    if (lane + o < 64) above += y;
+  }
+  above -= mine;
+  auto quantile = [&](uint32_t want) {
+    int b = -1;
+    uint32_t acc = above;
+    for (int x = 3; x >= 0; --x) {
+      acc += tot[4 * lane + x];
+      if (b < 0 && acc >= want) b = 4 * lane + x;
+    }
+    const unsigned long long m = __ballot(b >= 0);   // lane 0 counts all N values, so never empty
+    return __shfl(b, 63 - __clzll((long long)m));
+  };
+  const int hi = quantile((uint32_t)N / 16), med = quantile((uint32_t)N / 2);
+  if (lane == 0) even[r] = hi - med < kEvenBins ? 1u : 0u;
+}
+
 // Fold-tile prefixes (one F task per kFRows tokens of a request), the state,
-// the counters. One block.
+// the counters; the form, where the device chooses it: the matrix (1) if any
+// request's relevance is too even. One block.
 __global__ __launch_bounds__(1024) void k_rprep(const int32_t *__restrict__ cu_vis, int R, int64_t *__restrict__ ftoff,
                                                 int32_t *__restrict__ st, uint32_t *__restrict__ dcnt,
                                                 unsigned long long *__restrict__ head, uint32_t *__restrict__ live,
-                                                uint32_t *__restrict__ abort_word) {
+                                                uint32_t *__restrict__ abort_word, const uint32_t *__restrict__ even,
+                                                uint32_t *__restrict__ form) {
   __shared__ int64_t sh[16];
   __shared__ int64_t s_run;
+  __shared__ uint32_t s_form;
   if (threadIdx.x == 0) {
     s_run = 0;
+    s_form = 0u;
     *head = 0ull;
     *live = (uint32_t)R;
     *abort_word = 0u;
   }
   __syncthreads();
+  if (form) {
+    for (int r = threadIdx.x; r < R; r += blockDim.x)
+      if (even[r] != 0u) s_form = 1u;
+    __syncthreads();
+    if (threadIdx.x == 0) *form = s_form;
+  }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   for (int base = 0; base < R; base += blockDim.x) {
     const int r = base + (int)threadIdx.x;
@@ -1076,6 +1164,7 @@ __global__ __launch_bounds__(kRThreads) void k_rounds(RArgs a) {
   __shared__ int shi[kRWaves];
   __shared__ int s_task[5];   // status (0 run, 2 exit), request, kind, sub-index, round
   __shared__ int s_ft[kFtLds];   // fold-tile prefixes of batches of fewer than kFtLds requests
+  if (a.form && *a.form != 0u) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = uni(tid >> 6);
   if (a.R < kFtLds)
@@ -1205,12 +1294,21 @@ bool rounds_supported(int32_t N_max, int32_t Dv, last_dtype fdtype) {
          (int64_t)N_max * Dv * 2 < ((int64_t)1 << 32);
 }
 
+hipError_t launch_round_prep(int32_t R, const SelectWs &w, const float *scores, const int32_t *cu_vis, hipStream_t s) {
+  launch_begin("rounds_prep", s);
+  if (w.form) hipLaunchKernelGGL(k_reven, dim3((unsigned)R), dim3(kEvenThreads), 0, s, scores, cu_vis, w.even);
+  uint32_t *live = reinterpret_cast<uint32_t *>(w.r_ctl + 1);
+  hipLaunchKernelGGL(k_rprep, dim3(1), dim3(1024), 0, s, cu_vis, R, w.r_qoff, w.r_st, w.r_dcnt, w.r_ctl, live, live + 1,
+                     w.even, w.form);
+  return launch_end(s);
+}
+
 hipError_t launch_round_norms(int32_t Dv, const SelectPlan &p, const SelectWs &w, const void *feats,
                               hipStream_t s) {
   if (p.N_total == 0) return hipSuccess;
   launch_begin("norms", s);
   hipLaunchKernelGGL(k_rnorm, dim3((unsigned)((p.N_total + 127) / 128)), dim3(256), 0, s,
-                     static_cast<const uint16_t *>(feats), p.N_total, Dv, w.nn, w.inv);
+                     static_cast<const uint16_t *>(feats), p.N_total, Dv, w.form, w.nn, w.inv);
   return launch_end(s);
 }
 
@@ -1237,6 +1335,7 @@ hipError_t launch_round_pick(int32_t R, int32_t Dv, const SelectPlan &p, const S
   a.st_T = w.r_T;
   a.dcnt = w.r_dcnt;
   a.ftoff = w.r_qoff;
+  a.form = w.form;
   a.head = w.r_ctl;
   a.live = reinterpret_cast<uint32_t *>(w.r_ctl + 1);
   a.abort_word = reinterpret_cast<uint32_t *>(w.r_ctl + 1) + 1;
@@ -1247,8 +1346,6 @@ hipError_t launch_round_pick(int32_t R, int32_t Dv, const SelectPlan &p, const S
   a.Q = Q;
   a.limit = device_wall_khz() * wait_us / 1000;
   launch_begin("rounds", s);
-  hipLaunchKernelGGL(k_rprep, dim3(1), dim3(1024), 0, s, cu_vis, R, w.r_qoff, w.r_st, w.r_dcnt, a.head, a.live,
-                     a.abort_word);
   hipLaunchKernelGGL(k_rounds, dim3((unsigned)grid), dim3(kRThreads), 0, s, a);
   hipLaunchKernelGGL(k_rfail, dim3((unsigned)std::min(R, 1024)), dim3(256), 0, s, a.abort_word, w.r_st, cu_keep, R,
                      kept, order, gains);

@@ -72,20 +72,24 @@ __device__ void compact_ascending(Flag flag, int32_t *dst, int *sh, int32_t valu
 // ascending index order; the block then takes the maximum 64-bit key
 // (objective bits, ~index), which orders by objective and breaks ties towards
 // the lowest index (objectives are >= 0 here, so their bits order like them).
-// req_order (nullable): block b takes the request of rank rank0 + b.
-template <int EPT, int NTH>
+// req_order (nullable): block b takes the request of rank rank0 + b. BY: the
+// form was chosen on the device, and the blocks return where it is the rounds
+// (a template, since the look at a null pointer costs a small batch 0.2 us).
+template <int EPT, int NTH, bool BY = false>
 __global__ __launch_bounds__(NTH) void k_greedy(const float *__restrict__ scores,
                                                 const float *__restrict__ dmat,
                                                 const int64_t *__restrict__ d_off,
                                                 const int32_t *__restrict__ cu_vis,
                                                 const int32_t *__restrict__ cu_keep,
                                                 const int32_t *__restrict__ req_order, int rank0,
+                                                const uint32_t *__restrict__ form,
                                                 int32_t *__restrict__ kept,
                                                 int32_t *__restrict__ order,
                                                 float *__restrict__ gains) {
   constexpr int kNW = NTH / 64;
   __shared__ unsigned long long s_key[2][kNW];
   __shared__ int s_cnt[16];
+  if (BY && *form == 0u) return;
   const int r = req_order ? req_order[rank0 + (int)blockIdx.x] : (int)blockIdx.x;
   const int64_t n0 = cu_vis[r];
   const int N = cu_vis[r + 1] - (int)n0;
@@ -782,58 +786,80 @@ static void greedy_shape(int32_t n, int32_t nreq, int32_t budget, int32_t *threa
 // The k-center's form: the matrix (gram.hip + the greedy here) or the rounds
 // (rounds.hip). LAST_KCENTER_FORM=gram or =rounds, read at every call, forces
 // one (rounds only where rounds_supported). By default the rounds take every
-// batch whose requests all have kRoundAutoN tokens or more, and others where
-// rounds_estimate says so.
+// batch whose requests all have kRoundAutoN tokens or more, and others by the
+// estimate below.
 //
 // The estimate (microseconds, 256 compute units) weighs what each form does:
 //   matrix: N_r^2 / 2 distances as Gram tiles of 0.8 us per 64 columns + 3
 //     us, then K_r dependent steps of 0.6 us + 0.11 us per 1000 tokens;
-//   rounds: K_r / 128 certified rounds if every round took its 128 picks,
-//     1.1 to 2 times that as the relevance goes from peaked to uniform (1.9
-//     is used). A round folds each 256-token tile (12 us + 19.5 us per 1000
-//     columns, all units busy), and a request's rounds follow one another,
-//     each a chain of select, candidate distances, greedy and fold.
-// Fitted on uniform batches of 256 to 16384 tokens, 1 to 128 requests, three
-// widths, both kinds of relevance (deviation about 25%); the rounds are taken
-// at 0.9 of the matrix's estimate. Where that holds they measured 1.15 to 5
-// times faster on peaked relevance and 0.75 (128 x 1024 tokens) to 3 times on
-// uniform relevance, which the host cannot tell apart. Measured either side
-// (matrix / rounds, us): 32 x 2880 tokens, 4096 wide, 1/9 kept: 1941 / 1127
-// (uniform relevance 1973; 1904 / 2161 where it deviates by 1% only); 64 x
-// 576: 245 / 417; 8 x 4096, 3584 wide, 1/16: 988 / 741 (1461 uniform; the
-// matrix stays); 128 ragged requests of 256 to 16384, 1536 wide, 1/8: 12980 /
-// 4960. A larger budget needs more rounds and the same matrix, so the form
-// depends on the budgets, and the workspace is the matrix form's.
-static bool rounds_estimate(int32_t R, const int32_t *cu_vis_h, const int32_t *cu_keep_h, int32_t Dv) {
-  double tiles = 0, folds = 0, chain = 0, greedy = 0, N_max = 0;
+//   rounds: 1 + `more` K_r / 128 certified rounds. A round is a chain of
+//     select, candidate distances, greedy (pick_us) and the folds of the
+//     request's 256-token tiles (12 us + 19.5 us per 1000 columns each); all
+//     of it is work for the units, and a request's rounds follow one another.
+// How many rounds a batch takes depends on its relevance and features: `more`
+// is 1.2 to 1.9 where the relevance has peaks, up to 3 and over where it is
+// even, or where whole clusters of near copies share their relevance. The host
+// sees neither, so there are three answers:
+//   - the rounds, where they win even with kMoreEven (matrix / rounds, us, for
+//     relevance with peaks, even to 1%, and following the features so that near
+//     copies share theirs): 128 ragged requests of 256 to 16384 tokens, 1536
+//     wide, 1/8 kept: 13000 / 5230, 6930, 10400; 16 x 8000, 4096 wide, 1/8:
+//     8230 / 3040, 3730, 5610; 32 x 4096, 3584 wide, 1/16: 2930 / 1160, 1740,
+//     2610;
+//   - where they win with kMoreFew only, and the matrix form is one launch of
+//     each kernel, the device chooses by the relevance: the matrix where it is
+//     even (k_reven). 32 x 2880, 4096 wide, 1/9: 1930 / 1090 to 1160, 1670,
+//     1680; 64 x 1500, 3584 wide, 1/16: 980 / 630, 910, 700. What the relevance
+//     does not show still costs up to 1.4 times: on frames that drift slowly,
+//     relevance that follows the features takes 32 x 2880 tokens 1910 / 2450,
+//     16 x 4096 (3584 wide, 1/16) 1600 / 2200;
+//   - else the matrix: 64 x 576: 245 / 417; 8 x 4096, 3584 wide, 1/16: 970 /
+//     720, 1200, 2030; 128 x 1024, 4096 wide, 1/9: 970 / 920, 1490, 1280; 4 x
+//     8000, 4096 wide, 1/8: 3110 / 2050, 2560, 4120.
+// A larger budget needs more rounds and the same matrix, so the form depends on
+// the budgets; the workspace is the matrix form's for all of these.
+constexpr double kMoreEven = 3.0, kMoreFew = 1.9;
+static void form_estimate(int32_t R, const int32_t *cu_vis_h, const int32_t *cu_keep_h, int32_t Dv, double more,
+                          double *matrix_us, double *rounds_us) {
+  double tiles = 0, work = 0, chain = 0, greedy = 0, N_max = 0;
   const double fold_us = 12 + 0.0195 * Dv;
   for (int r = 0; r < R; ++r) {
     const double N = cu_vis_h[r + 1] - cu_vis_h[r], K = cu_keep_h[r + 1] - cu_keep_h[r];
-    const double nb = ceil(N / kTile), rounds = 1 + 1.9 * K / kRoundPicks;
+    const double nb = ceil(N / kTile), rounds = 1 + more * K / kRoundPicks;
     N_max = std::max(N_max, N);
     tiles += nb * (nb - 1) / 2;
     greedy = std::max(greedy, K * (0.6 + 1.1e-4 * N));
-    folds += ceil(N / kRoundFoldRows) * rounds;
-    chain = std::max(chain, rounds * (42 + N / 1300 + 0.012 * Dv + 0.25 * std::min<double>(kRoundPicks, K) + fold_us));
+    const double pick_us = 42 + N / 1300 + 0.012 * Dv + 0.25 * std::min<double>(kRoundPicks, K);
+    work += rounds * (pick_us + ceil(N / kRoundFoldRows) * fold_us);
+    chain = std::max(chain, rounds * (pick_us + fold_us));
   }
-  const double cus = device_cus(), gram = tiles * (0.8 * Dv / 64 + 3) / cus, fold = folds * fold_us / cus;
+  const double cus = device_cus(), gram = tiles * (0.8 * Dv / 64 + 3) / cus;
+  work /= cus;
   // a ragged batch's greedies run beside the rest of its Gram: about half is hidden
   const bool ragged = N_max > 2.0 * cu_vis_h[R] / R;
-  const double matrix = gram + greedy * std::max(1.0, R / cus) * (ragged ? 0.5 : 1.0);
-  return std::max(fold, chain) + 0.35 * std::min(fold, chain) < 0.9 * matrix;
+  *matrix_us = gram + greedy * std::max(1.0, R / cus) * (ragged ? 0.5 : 1.0);
+  *rounds_us = std::max(work, chain) + 0.35 * std::min(work, chain);
 }
 
-static bool want_rounds(RoundsRule rule, int32_t R, const int32_t *cu_vis_h, const int32_t *cu_keep_h, int32_t N_min,
-                        int32_t N_max, int32_t Dv, last_dtype fdtype, bool *by_budget) {
+enum Form { kFormMatrix, kFormRounds, kFormByRelevance };
+static Form kcenter_form(RoundsRule rule, int32_t R, const int32_t *cu_vis_h, const int32_t *cu_keep_h, int32_t N_min,
+                         int32_t N_max, int32_t Dv, last_dtype fdtype, bool *by_budget) {
   *by_budget = false;
-  if (rule == kRoundsNever || !rounds_supported(N_max, Dv, fdtype)) return false;
+  if (rule == kRoundsNever || !rounds_supported(N_max, Dv, fdtype)) return kFormMatrix;
   if (const char *env = getenv("LAST_KCENTER_FORM")) {
-    if (strcmp(env, "gram") == 0) return false;
-    if (strcmp(env, "rounds") == 0) return true;
+    if (strcmp(env, "gram") == 0) return kFormMatrix;
+    if (strcmp(env, "rounds") == 0) return kFormRounds;
   }
-  if (N_min >= kRoundAutoN) return true;
-  *by_budget = rule == kRoundsAny && rounds_estimate(R, cu_vis_h, cu_keep_h, Dv);
-  return *by_budget;
+  if (N_min >= kRoundAutoN) return kFormRounds;
+  if (rule != kRoundsAny) return kFormMatrix;
+  double matrix, rounds;
+  form_estimate(R, cu_vis_h, cu_keep_h, Dv, kMoreEven, &matrix, &rounds);
+  if (rounds < 0.9 * matrix) {
+    *by_budget = true;
+    return kFormRounds;
+  }
+  form_estimate(R, cu_vis_h, cu_keep_h, Dv, kMoreFew, &matrix, &rounds);
+  return rounds < 0.95 * matrix ? kFormByRelevance : kFormMatrix;
 }
 
 SelectPlan make_select_plan(int32_t R, const int32_t *cu_vis_h, const int32_t *cu_keep_h,
@@ -866,13 +892,15 @@ SelectPlan make_select_plan(int32_t R, const int32_t *cu_vis_h, const int32_t *c
   p.group_slices[0] = p.g_slices;
   int32_t N_min = p.N_max;
   for (int r = 0; r < R; ++r) N_min = std::min<int32_t>(N_min, cu_vis_h[r + 1] - cu_vis_h[r]);
-  if (mode == LAST_SEL_KCENTER &&
-      want_rounds(rounds, R, cu_vis_h, cu_keep_h, N_min, p.N_max, Dv, fdtype, &p.rounds_by_budget)) {
-    p.rounds = true;
-    for (int r = 0; r < R; ++r)
-      p.round_Q += 2 + (cu_vis_h[r + 1] - cu_vis_h[r] + kRoundFoldRows - 1) / kRoundFoldRows;
-    return p;
-  }
+  const Form form = mode != LAST_SEL_KCENTER ? kFormMatrix
+                                             : kcenter_form(rounds, R, cu_vis_h, cu_keep_h, N_min, p.N_max, Dv, fdtype,
+                                                            &p.rounds_by_budget);
+  for (int r = 0; r < R; ++r)
+    p.round_Q += 2 + (cu_vis_h[r + 1] - cu_vis_h[r] + kRoundFoldRows - 1) / kRoundFoldRows;
+  p.rounds = form == kFormRounds;
+  if (p.rounds) return p;
+  // (256 and 512 threads: the greedies that look at the form)
+  p.by_relevance = form == kFormByRelevance && p.g_slices == 0 && (p.g_threads == 256 || p.g_threads == 512);
   if (!allow_groups || mode != LAST_SEL_KCENTER || R < 2 || R > kRankMaxR) return p;
 
   // Ragged batches. A greedy takes about K_r (0.6 + 1.1e-4 N_r) microseconds
@@ -1031,6 +1059,7 @@ SelectPlan make_select_plan(int32_t R, const int32_t *cu_vis_h, const int32_t *c
     p.group_tile0[g] = cum[best.rank0[g]];
   }
   p.ranked = true;
+  p.by_relevance = false;
   p.reserve = best.reserve;
   // a group's greedies run beside the later groups' Gram, on the compute units
   // it leaves free
@@ -1044,6 +1073,7 @@ SelectWs carve_select_ws(void *ws, int32_t R, const SelectPlan &p, last_sel_mode
                          size_t *bytes) {
   Carver cv(ws);
   SelectWs w{};
+  w.base = ws;
   if (mode == LAST_SEL_KCENTER && p.rounds) {
     w.nn = cv.take<double>(p.N_total + kTile);
     w.inv = cv.take<double>(p.N_total + kTile);
@@ -1066,6 +1096,10 @@ SelectWs carve_select_ws(void *ws, int32_t R, const SelectPlan &p, last_sel_mode
     w.dmat = cv.take<float>(p.d_elems);
     w.req_order = cv.take<int32_t>(R);
     w.mc_slots = cv.take<unsigned long long>((int64_t)R * kMcSlotWords);
+    if (p.by_relevance) {   // such a plan has no multi-block greedy: its words are free
+      w.form = reinterpret_cast<uint32_t *>(w.mc_slots);
+      w.even = w.form + 1;
+    }
   }
   *bytes = cv.size();
   return w;
@@ -1082,15 +1116,46 @@ static hipError_t launch_pipelined(int32_t R, int32_t Dv, const SelectPlan &p, c
                                    const int32_t *cu_keep, int32_t *kept, int32_t *order, float *gains,
                                    hipStream_t s);
 
+static hipError_t launch_rounds(int32_t R, int32_t Dv, const SelectPlan &p, const SelectWs &w, const float *scores,
+                                const void *feats, const int32_t *cu_vis, const int32_t *cu_keep, int32_t *kept,
+                                int32_t *order, float *gains, hipStream_t s) {
+  hipError_t e = launch_round_prep(R, w, scores, cu_vis, s);
+  if (e == hipSuccess) e = launch_round_norms(Dv, p, w, feats, s);
+  if (e == hipSuccess) e = launch_round_pick(R, Dv, p, w, scores, feats, cu_vis, cu_keep, kept, order, gains, s);
+  return e;
+}
+
+// Both forms, of which the kernels of one return at once: w.form, which
+// launch_round_prep sets on the device, says which (the empty launches are
+// about 20 us). The rounds' workspace lies over the matrix form's, which is
+// larger (a request's coverage matrix alone takes 64 KB or more for every 128
+// tokens, the rounds' own part of it 4 bytes a token and 1.3 KB) and holds the
+// word behind the matrices.
+static hipError_t launch_by_relevance(int32_t R, int32_t Dv, last_dtype fdtype, const SelectPlan &p, const SelectWs &w,
+                                      const float *scores, const void *feats, const int32_t *cu_vis,
+                                      const int32_t *cu_keep, int32_t *kept, int32_t *order, float *gains,
+                                      hipStream_t s) {
+  SelectPlan rp = p;
+  rp.rounds = true;
+  size_t bytes = 0;
+  SelectWs rw = carve_select_ws(w.base, R, rp, LAST_SEL_KCENTER, &bytes);
+  if (static_cast<char *>(w.base) + bytes > reinterpret_cast<char *>(w.form)) return hipErrorInvalidValue;
+  rw.form = w.form;
+  rw.even = w.even;
+  hipError_t e = launch_rounds(R, Dv, rp, rw, scores, feats, cu_vis, cu_keep, kept, order, gains, s);
+  if (e == hipSuccess) e = launch_similarity(R, Dv, fdtype, p, w, feats, cu_vis, s);
+  if (e == hipSuccess) e = launch_pick(R, LAST_SEL_KCENTER, p, w, scores, cu_vis, cu_keep, kept, order, gains, s);
+  return e;
+}
+
 hipError_t launch_select(int32_t R, int32_t Dv, last_dtype fdtype, last_sel_mode mode,
                          const SelectPlan &p, const SelectWs &w, const float *scores,
                          const void *feats, const int32_t *cu_vis, const int32_t *cu_keep,
                          int32_t *kept, int32_t *order, float *gains, hipStream_t s) {
-  if (mode == LAST_SEL_KCENTER && p.rounds) {
-    const hipError_t e = launch_round_norms(Dv, p, w, feats, s);
-    if (e != hipSuccess) return e;
-    return launch_round_pick(R, Dv, p, w, scores, feats, cu_vis, cu_keep, kept, order, gains, s);
-  }
+  if (mode == LAST_SEL_KCENTER && p.rounds)
+    return launch_rounds(R, Dv, p, w, scores, feats, cu_vis, cu_keep, kept, order, gains, s);
+  if (mode == LAST_SEL_KCENTER && p.by_relevance)
+    return launch_by_relevance(R, Dv, fdtype, p, w, scores, feats, cu_vis, cu_keep, kept, order, gains, s);
   if (mode == LAST_SEL_KCENTER && p.groups > 1 && gram_streamed(fdtype, Dv))
     return launch_pipelined(R, Dv, p, w, scores, feats, cu_vis, cu_keep, kept, order, gains, s);
   if (mode == LAST_SEL_KCENTER) {
@@ -1203,9 +1268,13 @@ static hipError_t launch_greedy(int32_t threads, int32_t ept, int32_t slices, in
     const hipError_t e2 = launch_end(s);
     return e != hipSuccess ? e : e2;
   }
-#define LAST_GREEDY(E, T)                                                                          \
-  hipLaunchKernelGGL((k_greedy<E, T>), dim3(blocks), dim3(T), 0, s, scores, w.dmat, w.d_off, cu_vis, cu_keep, \
-                     req_order, rank0, kept, order, gains)
+#define LAST_GREEDY_K(E, T, BY)                                                                    \
+  hipLaunchKernelGGL((k_greedy<E, T, BY>), dim3(blocks), dim3(T), 0, s, scores, w.dmat, w.d_off, cu_vis, cu_keep, \
+                     req_order, rank0, w.form, kept, order, gains)
+#define LAST_GREEDY(E, T) LAST_GREEDY_K(E, T, false)
+#define LAST_GREEDY_BY(E, T)                                  \
+  if (w.form) LAST_GREEDY_K(E, T, true);                      \
+  else LAST_GREEDY_K(E, T, false)
   if (threads == 64) {
     switch (ept) {
       case 2: LAST_GREEDY(2, 64); break;
@@ -1220,16 +1289,18 @@ static hipError_t launch_greedy(int32_t threads, int32_t ept, int32_t slices, in
     }
   } else if (threads == 256) {
     switch (ept) {
-      case 8: LAST_GREEDY(8, 256); break;
-      case 16: LAST_GREEDY(16, 256); break;
-      default: LAST_GREEDY(32, 256); break;
+      case 8: LAST_GREEDY_BY(8, 256); break;
+      case 16: LAST_GREEDY_BY(16, 256); break;
+      default: LAST_GREEDY_BY(32, 256); break;
     }
   } else if (threads == 512) {
-    LAST_GREEDY(32, 512);
+    LAST_GREEDY_BY(32, 512);
   } else {
     LAST_GREEDY(32, 1024);
   }
+#undef LAST_GREEDY_BY
 #undef LAST_GREEDY
+#undef LAST_GREEDY_K
   return launch_end(s);
 }
 

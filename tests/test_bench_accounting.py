@@ -153,3 +153,10 @@ def test_rounds_kernels_accounting():
     assert abs(sm["tflops_on_paper_work"] - sw["similarity_flops"] / 6.4e-3 / 1e12) < 0.01
     assert bench.kcenter_form(kernels) == "rounds"
     assert bench.kcenter_form({"gram": {}}) == "matrix" and bench.kcenter_form({"topk": {}}) is None
+    # a form chosen on the device: both are launched, the other's kernels return at once
+    both = {k: {"ms_per_step": ms} for k, ms in (("norms", 0.004), ("rounds", 0.01), ("gram_diag", 0.3), ("gram", 1.2),
+                                                 ("greedy", 0.3))}
+    assert bench.kcenter_form(both) == "matrix" and set(bench.form_not_taken(both)) == {"norms", "rounds"}
+    assert bench.similarity_summary(W.make("c3_llava_next"), both)["form"] == "matrix"
+    both["rounds"]["ms_per_step"] = 2.0
+    assert bench.kcenter_form(both) == "rounds" and set(bench.form_not_taken(both)) == {"gram_diag", "gram", "greedy"}

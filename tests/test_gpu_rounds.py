@@ -322,3 +322,72 @@ def test_rounds_one_slow_request(R, N, K, Dv):
     cv, ck = (np.arange(R + 1) * N).astype(np.int32), (np.arange(R + 1) * K).astype(np.int32)
     kept, _, _ = both(feats.bfloat16(), w, cv, ck, f"slow request {R} x {N}")
     assert (kept >= 0).all()
+
+
+def _relevance_batch(Dv=4096, lengths=(2880,) * 31 + (150,), kept=(1, 9)):
+    """A batch whose form depends on its relevance, and relevance of several
+    kinds (a request of at most 192 tokens among them counts for none)."""
+    n = np.array(lengths)
+    cv = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    ck = np.concatenate([[0], np.cumsum(-(-n * kept[0] // kept[1]))]).astype(np.int32)
+    gen = torch.Generator("cuda").manual_seed(int(cv[-1]))
+    N = int(cv[-1])
+    feats = torch.randn((N, Dv), device="cuda", generator=gen).bfloat16()
+    z = torch.randn(N, device="cuda", generator=gen)
+    kinds = {"even": 1 + 0.001 * z, "peaked": torch.exp(0.5 * z), "zero": torch.zeros(N, device="cuda"),
+             "one_even": torch.exp(0.5 * z), "huge": torch.exp(0.5 * z)}
+    kinds["one_even"][cv[3]:cv[4]] = 2.0 + 0.001 * z[cv[3]:cv[4]]
+    kinds["huge"] *= 3e38 / kinds["huge"].max()   # their sum is infinite
+    kinds["huge"][cv[1] + 7], kinds["huge"][cv[2] + 9], kinds["huge"][cv[5] + 1] = np.inf, np.nan, -1.0
+    return feats, cv, ck, kinds
+
+
+def test_form_by_relevance():
+    """Batches whose faster form depends on the relevance: the rounds where it
+    has peaks, the matrix where any request's is even, the matrix form's bits
+    either way. A wait limit of 0 tells which form answered: only the rounds
+    wait, and then mark what they did not finish."""
+    feats, cv, ck, kinds = _relevance_batch()
+    os.environ.pop("LAST_KCENTER_FORM", None)
+    ws = torch.empty(last.select_workspace(cv, feats.shape[1]), dtype=torch.uint8, device="cuda")
+    for kind, w in kinds.items():
+        want = select("gram", feats, w, cv, ck)
+        got = [x.cpu().numpy() for x in last.diverse_select(w, feats, cv, ck, ws=ws)]
+        for a, b in zip(got, want):
+            assert np.array_equal(a.view(np.uint32), b.view(np.uint32)), kind
+        with env(LAST_MC_WAIT_US=0):
+            kept = last.diverse_select(w, feats, cv, ck, ws=ws)[0].cpu().numpy()
+        if kind in ("peaked", "huge"):
+            assert (kept < 0).any(), f"{kind}: the matrix answered"
+        else:
+            assert np.array_equal(kept, want[0]), f"{kind}: the rounds answered"
+
+
+def test_form_by_relevance_in_a_graph():
+    """The choice is made on the device, so one captured call follows the
+    relevance it is replayed with."""
+    feats, cv, ck, kinds = _relevance_batch(Dv=1536, lengths=(2880,) * 64)
+    os.environ.pop("LAST_KCENTER_FORM", None)
+    ws = torch.empty(last.select_workspace(cv, feats.shape[1]), dtype=torch.uint8, device="cuda")
+    w = kinds["peaked"].clone()
+    dev = [torch.from_numpy(x).cuda() for x in (cv, ck)]
+    out = [torch.empty(int(ck[-1]), dtype=t, device="cuda") for t in (torch.int32, torch.int32, torch.float32)]
+    call = lambda: last.diverse_select(w, feats, cv, ck, cu_vis=dev[0], cu_keep=dev[1], kept=out[0], order=out[1],
+                                       gains=out[2], ws=ws)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        call()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for kind in ("peaked", "even", "peaked", "one_even", "even", "peaked"):
+        w.copy_(kinds[kind])
+        for x in out:
+            x.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(out, select("gram", feats, kinds[kind], cv, ck)):
+            assert np.array_equal(a.cpu().numpy().view(np.uint32), b.view(np.uint32)), kind
