@@ -454,7 +454,11 @@ __global__ __launch_bounds__(kThreads, 2) void k_prefill(
         w.y = pack_bf16(o[dt][e + 2] * inv, o[dt][e + 3] * inv);
         reinterpret_cast<uint2 *>(rows + col * NP + pswz<NP>(col, d >> 3))[half] = w;
       }
-    // (the wave's own rows: its LDS operations complete in order)
+    // (the wave's own rows: its LDS operations complete in order; the fence
+    // keeps the compiler from moving the loads, of other lanes' pieces, above
+    // the stores)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     uint16_t *ob = out + (((int64_t)l * T_total + tok0 + q0) * Hq + h) * DH;
 #pragma unroll 4
     for (int x = 0; x < NP / 2; ++x) {
