@@ -237,8 +237,8 @@ size_t diverse_select_workspace(int32_t R, const int32_t *cu_vis_h, int32_t Dv,
  *                17 GB at 65536 tokens, 69 GB at 131072), then the greedy;
  *              - the rounds (bf16 features, Dv a multiple of 256 up to 4096,
  *                N_r <= 32768): only the distances to the tokens picked (the
- *                paper's O(K N d_v) form, about 20 bytes of workspace per
- *                token and 2 KB per request), computed for up to 128 picks at
+ *                paper's O(K N d_v) form, about 28 bytes of workspace per
+ *                token and 1.3 KB per request), computed for up to 128 picks at
  *                a time; the picks of a round are certified exact against
  *                every token outside its 192 candidates.
  *              By default the rounds take batches whose every request has

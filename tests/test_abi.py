@@ -178,7 +178,7 @@ def test_select_workspace_and_small_workspace():
 
 def test_kcenter_form_and_workspace(monkeypatch):
     """The k-center's form decides its workspace: the rounds keep no N x N
-    matrix (about 1 KB a token and 148 KB a request), the matrix form 4 N_r^2
+    matrix (28 bytes a token and 1.3 KB a request), the matrix form 4 N_r^2
     bytes. By default the rounds take batches whose every request has 8192
     tokens or more (bf16, Dv a multiple of 256 up to 4096, N_r <= 32768);
     LAST_KCENTER_FORM forces either; the two-call form always keeps the
@@ -190,7 +190,9 @@ def test_kcenter_form_and_workspace(monkeypatch):
     def ws(cv, Dv=3584, dt=last.LAST_BF16):
         return L.diverse_select_workspace(2, cv.ctypes.data, Dv, dt, last.KCENTER)
     monkeypatch.delenv("LAST_KCENTER_FORM", raising=False)
-    assert 0 < ws(long_) < 2 ** 20 * 40                    # rounds: no matrix
+    def rounds_bytes(cv):                                  # with 256-byte padding of a dozen arrays
+        return 28 * int(cv[-1]) + 1316 * (len(cv) - 1) + 2 * 8 * 128 + 13 * 256
+    assert 28 * 32768 < ws(long_) <= rounds_bytes(long_)   # rounds: no matrix
     assert ws(mixed) > (16384 ** 2) * 4                    # matrix form
     assert ws(long_, Dv=3600) > mat                        # Dv not a multiple of 256: matrix
     assert ws(long_, dt=last.LAST_F32) > mat               # fp32 features: matrix
@@ -200,9 +202,25 @@ def test_kcenter_form_and_workspace(monkeypatch):
     monkeypatch.setenv("LAST_KCENTER_FORM", "gram")
     assert ws(long_) == pair
     monkeypatch.setenv("LAST_KCENTER_FORM", "rounds")
-    assert ws(mixed) < 2 ** 20 * 40
+    assert ws(mixed) <= rounds_bytes(mixed)
     big = np.array([0, 32769], np.int32)                   # past the rounds' 32768 tokens: matrix
     assert L.diverse_select_workspace(1, big.ctypes.data, 256, last.LAST_BF16, last.KCENTER) > 32769 ** 2 * 4
+
+
+def test_estimated_forms_keep_the_matrix_workspace(monkeypatch):
+    """Batches whose form the budgets decide (the rounds outright, or by their
+    relevance on the device, or the matrix) all need what the query says, the
+    matrix form's size: one byte less is refused."""
+    monkeypatch.delenv("LAST_KCENTER_FORM", raising=False)
+    L = last.lib()
+    for R, N, Dv, keep in ((32, 4096, 3584, 256),      # rounds
+                           (32, 2880, 4096, 320),      # by the relevance
+                           (64, 576, 4096, 64)):       # matrix
+        cv, ck = (np.arange(R + 1) * N).astype(np.int32), (np.arange(R + 1) * keep).astype(np.int32)
+        need = L.diverse_select_workspace(R, cv.ctypes.data, Dv, last.LAST_BF16, last.KCENTER)
+        assert need == L.diverse_select_similarity_workspace(R, cv.ctypes.data, Dv, last.LAST_BF16)
+        assert need > 4 * R * N * N
+        assert _select_call(cv, ck, Dv=Dv, ws_bytes=need - 1) == last.LAST_ERR_WORKSPACE
 
 
 def _two_phase_call(phase, cv, ck, Dv=64, fdtype=last.LAST_BF16, ws_bytes=1 << 40, misalign=0):
