@@ -414,7 +414,8 @@ hipError_t launch_tile(const void *A, const void *B, const float *bias, int64_t 
 // full round (us for both 4096-wide products of last_connector); a round that
 // leaves units idle costs less, down to 0.8 of it. All are proportional to
 // the reduction length. Whole call, 4096 -> 4096 -> 4096, before (256 x 256
-// only) and with the tile chosen: 64 rows 184 -> 28.6 us (32 x 32), 96 rows
+// only) and with the tile chosen: 64 rows 186 -> 26.7 us (32 x 32; 209 -> 56 on
+// operands that no cache holds yet), 96 rows
 // 184 -> 33 (64 x 32), 256 rows 198 -> 43 (64 x 64), 1024 rows 200 -> 86 (128
 // x 128), 2048 rows 205 -> 145 (256 x 128), 4096 rows 250 (256 x 256 either
 // way; 308 with 128 x 128); 1536 wide, 1024 rows 101 -> 40.

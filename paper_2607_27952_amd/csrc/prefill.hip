@@ -37,16 +37,18 @@
 // and the sums stay as finite as the values; what was summed is rescaled only
 // when some lane's maximum has moved.
 //
-// What bounds it: the matrix cores at the clock the part's power allows. The
+// What bounds it: long sequences, the matrix and vector units sharing the
+// issue (matrix cores busy 53% of the cycles, at 1.93 GHz of 2.4 nominal, on 8 x
+// 16512 tokens); short ones, latency (busy 26% on 64 x 640). The
 // loop is pipelined by stages: the matrix cores form the next stage's logits
 // and then this stage's products with the values while the vector ALU forms
 // this stage's probabilities, and the next stage's maximum is taken under the
 // last products. 8 x 16512 tokens, 28/4 heads, one layer: 23.1 ms with the
-// same arithmetic one phase after the other, 14.9 now (1.05 PFLOP/s, where
+// same arithmetic one phase after the other, 15.3 now (1.02 PFLOP/s, where
 // torch's 8192^3 product reaches 1.22). 64 x 640 tokens, 32 heads, 2 layers:
 // 1.27 -> 0.88 ms. A reference that moves only past 2^16 instead of the
-// maximum took 14.5 and 0.87 ms, but rounds a row's largest probability and
-// lets values past 2^90 overflow. With the products one stage behind, the
+// maximum took 2% less, but rounds a row's largest probability and lets
+// values past 2^90 overflow. With the products one stage behind, the
 // registers spill (20.3 and 1.45 ms).
 #include <algorithm>
 #include <math.h>

@@ -47,14 +47,17 @@
 //              completed: no block ever waits for a block that has not started,
 //              so the grid needs no co-residency. Every wait is bounded by a
 //              wall-clock limit.
-//
-// What bounds it: the folds, which read X once a round (video batch, 8 x
-// 16384 tokens of 3584: 10.6 rounds of 128 picks, 5440 folds of 89 us on 256
-// units, 10 GB, 4.6 TB/s while folding), and the chain of one request's
-// rounds (S 23 us, G 89, F 89). Rounds of 64 picks needed 17 of them: 3.53 ms
-// against 2.53 for that batch, 10.9 against 4.7 ms for 128 ragged requests of
-// 256 to 16384 tokens (1536 wide), 1.52 against 1.01 for 32 x 2880 (4096).
 //   k_rfail    after a timeout, marks the unfinished requests invalid.
+//
+// What bounds it: the folds, which read X once a round, and the chain of one
+// request's rounds, on relevance with peaks. Video batch, 8 x 16384 tokens of
+// 3584: 10.6 rounds of up to 128 picks, each a chain of S 23 us, G 89 and F 89;
+// its 5440 folds on 256 units are 1.9 of the 2.5 ms; 10.1 GB fetched (4.0 TB/s
+// over the kernel), matrix cores busy 20%. 128 ragged requests of 256 to 16384
+// tokens of 1536: 15.3 GB in 4.7 ms, some 19400 folds of 42 us (3.2 ms over the
+// units), the longest request's chain about 2.9 ms, busy 15%. 32 x 2880 tokens
+// of 4096: 3.6 GB in 1.05 ms, busy 13%. Rounds of 64 picks took 3.53, 10.9 and
+// 1.52 ms.
 #include <algorithm>
 #include <cstdlib>
 #include <math.h>
