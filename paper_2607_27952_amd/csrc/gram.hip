@@ -74,13 +74,15 @@ __device__ void block_excl_scan_i64(int64_t v, int64_t *sh, int64_t *total, int6
 // in decreasing size (ties: lower index first), rank k being request
 // req_order[k], so that a ragged batch's largest requests finish their Gram
 // first; otherwise in request order.
-__global__ __launch_bounds__(256) void k_select_plan(const int32_t *__restrict__ cu_vis, int R, int ranked,
+__global__ __launch_bounds__(256) void k_select_plan(const int32_t *__restrict__ cu_vis,
+                                                     const uint32_t *__restrict__ form, int R, int ranked,
                                                      int32_t *__restrict__ dtile_off,
                                                      int32_t *__restrict__ otile_off,
                                                      int64_t *__restrict__ d_off,
                                                      int32_t *__restrict__ req_order) {
   __shared__ int64_t sh[4];
   __shared__ int32_t s_n[last::kRankMaxR], s_ord[last::kRankMaxR];
+  if (form && *form == 0u) return;
   int64_t carry_d = 0, carry_o = 0, carry_m = 0;
   for (int base = 0; base < R; base += 256) {
     const int r = base + (int)threadIdx.x;
@@ -217,12 +219,14 @@ __device__ void fill_request_tiles(const int32_t *__restrict__ cu_vis, int r, in
 // tiles that run together share few row blocks and re-read them from cache,
 // not HBM. The caps bound every write.
 __global__ __launch_bounds__(256) void k_tile_fill(const int32_t *__restrict__ cu_vis,
+                                                   const uint32_t *__restrict__ form,
                                                    const int32_t *__restrict__ dtile_off,
                                                    const int32_t *__restrict__ otile_off,
                                                    const int64_t *__restrict__ d_off,
                                                    int64_t diag_cap, int64_t off_cap,
                                                    TileMeta *__restrict__ dtile,
                                                    TileMeta *__restrict__ otile) {
+  if (form && *form == 0u) return;
   const int r = blockIdx.x, R = gridDim.x;
   fill_request_tiles(cu_vis, r, R, dtile_off[r], dtile_off[R], otile_off[r], d_off[r], diag_cap, off_cap, dtile,
                      otile);
@@ -1231,9 +1235,9 @@ hipError_t launch_gram_plan(int32_t R, const SelectPlan &p, const SelectWs &w, c
                        w.otile_off, w.d_off, w.dtile, w.otile);
     return launch_end(s);
   }
-  hipLaunchKernelGGL(k_select_plan, dim3(1), dim3(256), 0, s, cu_vis, R, 1, w.dtile_off, w.otile_off, w.d_off,
-                     w.req_order);
-  hipLaunchKernelGGL(k_tile_fill, dim3(R), dim3(256), 0, s, cu_vis, w.dtile_off, w.otile_off, w.d_off,
+  hipLaunchKernelGGL(k_select_plan, dim3(1), dim3(256), 0, s, cu_vis, w.form, R, 1, w.dtile_off, w.otile_off,
+                     w.d_off, w.req_order);
+  hipLaunchKernelGGL(k_tile_fill, dim3(R), dim3(256), 0, s, cu_vis, w.form, w.dtile_off, w.otile_off, w.d_off,
                      p.tiles_diag, p.tiles_off, w.dtile, w.otile);
   return launch_end(s);
 }

@@ -128,7 +128,8 @@ hipError_t launch_rows(const last_batch *b, const RowsPlan &p, const RowsWs &w,
 constexpr int kGramTile = 128;       // Gram tile edge (rows of X per side)
 constexpr int kSelMaxN = 131072;     // largest request diverse_select takes
 constexpr int kGreedyMaxN = 32768;   // largest request one block's registers hold (k_greedy, k_topk)
-constexpr int kMcSlotWords = 256;    // exchange words per request of the multi-block greedy
+constexpr int kMcSlotWords = 256;    // exchange words per request of the multi-block greedy,
+constexpr int kMcUsedWords = 193;    // of which it uses (and zeroes) the first ones
 
 // The k-center in rounds (rounds.hip), without the N x N matrix: candidates
 // a round, picks a round, tokens a fold task, and the largest Dv and N_r it
@@ -190,7 +191,7 @@ struct SelectPlan {
   int32_t group_slices[kMaxGroups];
   bool rounds;             // the k-center in rounds (rounds.hip) instead of the matrix
   bool rounds_by_budget;   // ... by the estimate: the workspace is still the matrix form's
-  bool by_relevance;       // the form is chosen on the device (launch_by_relevance); a plain matrix plan
+  bool by_relevance;       // the form is chosen on the device (launch_by_relevance); a matrix plan
   int64_t round_Q;         // tasks a round of the rounds kernel
 };
 
@@ -204,9 +205,11 @@ struct SelectWs {
   int32_t *req_order;              // [R] the request of each rank (ranked plans)
   unsigned long long *mc_slots;    // [R][kMcSlotWords] exchange words of the multi-block greedy, by rank
   void *base;                      // the workspace
-  // a form chosen on the device: its word (0 rounds, 1 matrix), and [R] whether a
-  // request's relevance is too even; null where the host chose
+  // a form chosen on the device: its word (0 rounds, 1 matrix), and whether request
+  // r's relevance is too even, at r kEvenStride; null where the host chose. They lie
+  // in words of mc_slots that the multi-block greedy leaves alone.
   uint32_t *form, *even;
+  static constexpr int64_t kEvenStride = 2 * kMcSlotWords;
   // the rounds form (nn and inv as above; nothing else of the matrix form)
   float *r_dl;                     // [N_total] running minimum coverage distance
   int32_t *r_cand, *r_picks;       // [R][kRoundCands], [R][kRoundPicks]

@@ -336,7 +336,7 @@ __global__ __launch_bounds__(256) void k_rnorm(const uint16_t *__restrict__ X, i
 }
 
 // ------------------------------------------------------------------- prep
-// even[r] = whether request r's relevance is too even for the rounds: its
+// even[r kEvenStride] = whether request r's relevance is too even for the rounds: its
 // N/16-th largest value within kEvenBins bins of its median, a bin being 1/32
 // of an octave (2 to 3%). The objectives of even relevance fall below the
 // bound after few picks of a round, whatever the features. (A request of at
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(kEvenThreads) void k_reven(const float *__restrict_
   const int64_t n0 = cu_vis[r];
   const int N = cu_vis[r + 1] - (int)n0;
   if (N <= kRB) {
-    if (tid == 0) even[r] = 0u;
+    if (tid == 0) even[r * SelectWs::kEvenStride] = 0u;
     return;
   }
   float sum = 0.f;
@@ -406,7 +406,7 @@ __global__ __launch_bounds__(kEvenThreads) void k_reven(const float *__restrict_
     return __shfl(b, 63 - __clzll((long long)m));
   };
   const int hi = quantile((uint32_t)N / 16), med = quantile((uint32_t)N / 2);
-  if (lane == 0) even[r] = hi - med < kEvenBins ? 1u : 0u;
+  if (lane == 0) even[r * SelectWs::kEvenStride] = hi - med < kEvenBins ? 1u : 0u;
 }
 
 // Fold-tile prefixes (one F task per kFRows tokens of a request), the state,
@@ -430,7 +430,7 @@ __global__ __launch_bounds__(1024) void k_rprep(const int32_t *__restrict__ cu_v
   __syncthreads();
   if (form) {
     for (int r = threadIdx.x; r < R; r += blockDim.x)
-      if (even[r] != 0u) s_form = 1u;
+      if (even[r * SelectWs::kEvenStride] != 0u) s_form = 1u;
     __syncthreads();
     if (threadIdx.x == 0) *form = s_form;
   }

@@ -264,15 +264,18 @@ __global__ __launch_bounds__(NTH) void k_greedy(const float *__restrict__ scores
 constexpr int kMcThreads = 256;
 constexpr int kMcMaxS = 64;                // slices a request (one per lane of the polling wave)
 constexpr int kMcSlotWords = last::kMcSlotWords;  // per request: two step parities, the counts, the abort word
-static_assert(kMcSlotWords == 4 * kMcMaxS, "exchange words: two step parities, the counts, the abort word");
+static_assert(last::kMcUsedWords == 3 * kMcMaxS + 1 && last::kMcUsedWords + 2 <= kMcSlotWords,
+              "exchange words: two step parities, the counts, the abort word; then the form's");
 
 __device__ __forceinline__ unsigned long long mc_key(unsigned tag, unsigned obits, int i) {
   return ((unsigned long long)tag << 62) | ((unsigned long long)obits << 30) |
          (unsigned long long)((1u << 30) - 1u - (unsigned)i);
 }
 
-__global__ __launch_bounds__(256) void k_zero_u64(unsigned long long *__restrict__ p, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0ull;
+// Zeroes the words the greedy uses in each request's exchange words.
+__global__ __launch_bounds__(256) void k_zero_slots(unsigned long long *__restrict__ p, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    if (i % kMcSlotWords < last::kMcUsedWords) p[i] = 0ull;
 }
 
 template <int EPT>
@@ -282,11 +285,12 @@ __global__ __launch_bounds__(kMcThreads) void k_greedy_mc(const float *__restric
                                                           const int32_t *__restrict__ cu_vis,
                                                           const int32_t *__restrict__ cu_keep,
                                                           const int32_t *__restrict__ req_order, int rank0, int nreq,
-                                                          int S, int spread,
+                                                          int S, int spread, const uint32_t *__restrict__ form,
                                                           unsigned long long *__restrict__ slots, int64_t limit,
                                                           int32_t *__restrict__ kept, int32_t *__restrict__ order,
                                                           float *__restrict__ gains) {
   constexpr int NTH = kMcThreads, kNW = NTH / 64, SL = NTH * EPT;
+  if (form && *form == 0u) return;
   __shared__ unsigned long long s_key[2][kNW];
   __shared__ unsigned long long s_pick, s_next;
   __shared__ float s_pre[2][SL];   // this slice of two prefetched coverage rows
@@ -806,13 +810,13 @@ static void greedy_shape(int32_t n, int32_t nreq, int32_t budget, int32_t *threa
 //     wide, 1/8 kept: 13000 / 5230, 6930, 10400; 16 x 8000, 4096 wide, 1/8:
 //     8230 / 3040, 3730, 5610; 32 x 4096, 3584 wide, 1/16: 2930 / 1160, 1740,
 //     2610;
-//   - where they win with kMoreFew only, and the matrix form is one launch of
-//     each kernel, the device chooses by the relevance: the matrix where it is
-//     even (k_reven). 32 x 2880, 4096 wide, 1/9: 1930 / 1090 to 1160, 1670,
-//     1680; 64 x 1500, 3584 wide, 1/16: 980 / 630, 910, 700. What the relevance
-//     does not show still costs up to 1.4 times: on frames that drift slowly,
-//     relevance that follows the features takes 32 x 2880 tokens 1910 / 2450,
-//     16 x 4096 (3584 wide, 1/16) 1600 / 2200;
+//   - where they win with kMoreFew only, the device chooses by the relevance:
+//     the matrix where it is even (k_reven). 32 x 2880, 4096 wide, 1/9: 1940 /
+//     1090 to 1180, 1670, 1680; 4 requests of 3777 to 15111, 1536 wide, 1/8:
+//     3800 / 1720, 2180, 2090; 37 x 1545, 3584 wide, 1/16: 650 / 520, 820, 590.
+//     What the relevance does not show still costs up to 1.4 times: on frames
+//     that drift slowly, relevance that follows the features takes 32 x 2880
+//     tokens 1910 / 2450, 16 x 4096 (3584 wide, 1/16) 1600 / 2200;
 //   - else the matrix: 64 x 576: 245 / 417; 8 x 4096, 3584 wide, 1/16: 970 /
 //     720, 1200, 2030; 128 x 1024, 4096 wide, 1/9: 970 / 920, 1490, 1280; 4 x
 //     8000, 4096 wide, 1/8: 3110 / 2050, 2560, 4120.
@@ -899,8 +903,7 @@ SelectPlan make_select_plan(int32_t R, const int32_t *cu_vis_h, const int32_t *c
     p.round_Q += 2 + (cu_vis_h[r + 1] - cu_vis_h[r] + kRoundFoldRows - 1) / kRoundFoldRows;
   p.rounds = form == kFormRounds;
   if (p.rounds) return p;
-  // (256 and 512 threads: the greedies that look at the form)
-  p.by_relevance = form == kFormByRelevance && p.g_slices == 0 && (p.g_threads == 256 || p.g_threads == 512);
+  p.by_relevance = form == kFormByRelevance;
   if (!allow_groups || mode != LAST_SEL_KCENTER || R < 2 || R > kRankMaxR) return p;
 
   // Ragged batches. A greedy takes about K_r (0.6 + 1.1e-4 N_r) microseconds
@@ -1059,7 +1062,6 @@ SelectPlan make_select_plan(int32_t R, const int32_t *cu_vis_h, const int32_t *c
     p.group_tile0[g] = cum[best.rank0[g]];
   }
   p.ranked = true;
-  p.by_relevance = false;
   p.reserve = best.reserve;
   // a group's greedies run beside the later groups' Gram, on the compute units
   // it leaves free
@@ -1096,9 +1098,9 @@ SelectWs carve_select_ws(void *ws, int32_t R, const SelectPlan &p, last_sel_mode
     w.dmat = cv.take<float>(p.d_elems);
     w.req_order = cv.take<int32_t>(R);
     w.mc_slots = cv.take<unsigned long long>((int64_t)R * kMcSlotWords);
-    if (p.by_relevance) {   // such a plan has no multi-block greedy: its words are free
-      w.form = reinterpret_cast<uint32_t *>(w.mc_slots);
-      w.even = w.form + 1;
+    if (p.by_relevance) {
+      w.form = reinterpret_cast<uint32_t *>(w.mc_slots + kMcUsedWords);
+      w.even = reinterpret_cast<uint32_t *>(w.mc_slots + kMcUsedWords + 1);
     }
   }
   *bytes = cv.size();
@@ -1126,8 +1128,8 @@ static hipError_t launch_rounds(int32_t R, int32_t Dv, const SelectPlan &p, cons
 }
 
 // Both forms, of which the kernels of one return at once: w.form, which
-// launch_round_prep sets on the device, says which (the empty launches are
-// about 20 us). The rounds' workspace lies over the matrix form's, which is
+// launch_round_prep sets on the device, says which (the empty launches take
+// about 20 us, 60 beside side streams). The rounds' workspace lies over the matrix form's, which is
 // larger (a request's coverage matrix alone takes 64 KB or more for every 128
 // tokens, the rounds' own part of it 4 bytes a token and 1.3 KB) and holds the
 // word behind the matrices.
@@ -1143,6 +1145,8 @@ static hipError_t launch_by_relevance(int32_t R, int32_t Dv, last_dtype fdtype, 
   rw.form = w.form;
   rw.even = w.even;
   hipError_t e = launch_rounds(R, Dv, rp, rw, scores, feats, cu_vis, cu_keep, kept, order, gains, s);
+  if (e == hipSuccess && p.groups > 1)
+    return launch_pipelined(R, Dv, p, w, scores, feats, cu_vis, cu_keep, kept, order, gains, s);
   if (e == hipSuccess) e = launch_similarity(R, Dv, fdtype, p, w, feats, cu_vis, s);
   if (e == hipSuccess) e = launch_pick(R, LAST_SEL_KCENTER, p, w, scores, cu_vis, cu_keep, kept, order, gains, s);
   return e;
@@ -1236,11 +1240,11 @@ static hipError_t launch_mc(int32_t slices, int32_t nreq, const int32_t *req_ord
     const int32_t n = std::min<int32_t>(per_launch, nreq - c);
     unsigned long long *slots = w.mc_slots + (int64_t)(rank0 + c) * kMcSlotWords;
     const int64_t words = (int64_t)n * kMcSlotWords;
-    hipLaunchKernelGGL(k_zero_u64, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 1024)), dim3(256), 0, s,
+    hipLaunchKernelGGL(k_zero_slots, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 1024)), dim3(256), 0, s,
                        slots, words);
     const unsigned grid = spread ? (unsigned)(n * slices) : (unsigned)(8 * slices * ((n + 7) / 8));
     hipLaunchKernelGGL(k_greedy_mc<EPT>, dim3(grid), dim3(kMcThreads), 0, s, scores, w.dmat, w.d_off, cu_vis,
-                       cu_keep, req_order, rank0 + c, n, slices, spread ? 1 : 0, w.mc_slots, limit, kept, order,
+                       cu_keep, req_order, rank0 + c, n, slices, spread ? 1 : 0, w.form, w.mc_slots, limit, kept, order,
                        gains);
   }
   return hipGetLastError();
@@ -1268,13 +1272,12 @@ static hipError_t launch_greedy(int32_t threads, int32_t ept, int32_t slices, in
     const hipError_t e2 = launch_end(s);
     return e != hipSuccess ? e : e2;
   }
-#define LAST_GREEDY_K(E, T, BY)                                                                    \
+#define LAST_GREEDY_BY(E, T, BY)                                                                   \
   hipLaunchKernelGGL((k_greedy<E, T, BY>), dim3(blocks), dim3(T), 0, s, scores, w.dmat, w.d_off, cu_vis, cu_keep, \
                      req_order, rank0, w.form, kept, order, gains)
-#define LAST_GREEDY(E, T) LAST_GREEDY_K(E, T, false)
-#define LAST_GREEDY_BY(E, T)                                  \
-  if (w.form) LAST_GREEDY_K(E, T, true);                      \
-  else LAST_GREEDY_K(E, T, false)
+#define LAST_GREEDY(E, T)                                                                          \
+  if (w.form) LAST_GREEDY_BY(E, T, true);                                                          \
+  else LAST_GREEDY_BY(E, T, false)
   if (threads == 64) {
     switch (ept) {
       case 2: LAST_GREEDY(2, 64); break;
@@ -1289,18 +1292,17 @@ static hipError_t launch_greedy(int32_t threads, int32_t ept, int32_t slices, in
     }
   } else if (threads == 256) {
     switch (ept) {
-      case 8: LAST_GREEDY_BY(8, 256); break;
-      case 16: LAST_GREEDY_BY(16, 256); break;
-      default: LAST_GREEDY_BY(32, 256); break;
+      case 8: LAST_GREEDY(8, 256); break;
+      case 16: LAST_GREEDY(16, 256); break;
+      default: LAST_GREEDY(32, 256); break;
     }
   } else if (threads == 512) {
-    LAST_GREEDY_BY(32, 512);
+    LAST_GREEDY(32, 512);
   } else {
     LAST_GREEDY(32, 1024);
   }
-#undef LAST_GREEDY_BY
 #undef LAST_GREEDY
-#undef LAST_GREEDY_K
+#undef LAST_GREEDY_BY
   return launch_end(s);
 }
 

@@ -336,30 +336,42 @@ def _relevance_batch(Dv=4096, lengths=(2880,) * 31 + (150,), kept=(1, 9)):
     z = torch.randn(N, device="cuda", generator=gen)
     kinds = {"even": 1 + 0.001 * z, "peaked": torch.exp(0.5 * z), "zero": torch.zeros(N, device="cuda"),
              "one_even": torch.exp(0.5 * z), "huge": torch.exp(0.5 * z)}
-    kinds["one_even"][cv[3]:cv[4]] = 2.0 + 0.001 * z[cv[3]:cv[4]]
+    kinds["one_even"][cv[4]:cv[5]] = 2.0 + 0.001 * z[cv[4]:cv[5]]
     kinds["huge"] *= 3e38 / kinds["huge"].max()   # their sum is infinite
-    kinds["huge"][cv[1] + 7], kinds["huge"][cv[2] + 9], kinds["huge"][cv[5] + 1] = np.inf, np.nan, -1.0
+    kinds["huge"][cv[1] + 7], kinds["huge"][cv[2] + 9], kinds["huge"][cv[4] + 1] = np.inf, np.nan, -1.0
     return feats, cv, ck, kinds
 
 
-def test_form_by_relevance():
+@pytest.mark.parametrize("Dv,lengths,kept", [
+    (4096, (2880,) * 31 + (150,), (1, 9)),                    # one launch of each of the matrix form's kernels
+    (1536, (4000, 5000, 7000, 150, 9000, 12000), (1, 8)),     # its greedy over several compute units
+    (1536, (8000,) * 8 + (1500,) * 11 + (150,), (1, 9)),      # its greedies on side streams
+    (1536, (12000,) * 6 + (2500,) * 20 + (150,), (1, 9)),     # both
+], ids=["plain", "multi_block", "side_streams", "both"])
+def test_form_by_relevance(Dv, lengths, kept):
     """Batches whose faster form depends on the relevance: the rounds where it
     has peaks, the matrix where any request's is even, the matrix form's bits
-    either way. A wait limit of 0 tells which form answered: only the rounds
-    wait, and then mark what they did not finish."""
-    feats, cv, ck, kinds = _relevance_batch()
+    either way. A wait limit of 0 tells which form answered: the rounds wait at
+    once, and then mark what they did not finish (and so does the greedy over
+    several compute units, which leaves only the rounds' answer to tell)."""
+    feats, cv, ck, kinds = _relevance_batch(Dv, lengths, kept)
     os.environ.pop("LAST_KCENTER_FORM", None)
     ws = torch.empty(last.select_workspace(cv, feats.shape[1]), dtype=torch.uint8, device="cuda")
     for kind, w in kinds.items():
         want = select("gram", feats, w, cv, ck)
+        last.profile_reset()
+        last.profile_enable(True)
         got = [x.cpu().numpy() for x in last.diverse_select(w, feats, cv, ck, ws=ws)]
+        took = {name for name, (count, _) in last.profile_collect().items() if count}
+        last.profile_enable(False)
+        assert {"rounds", "gram"} <= took, "the host chose the form"
         for a, b in zip(got, want):
             assert np.array_equal(a.view(np.uint32), b.view(np.uint32)), kind
         with env(LAST_MC_WAIT_US=0):
             kept = last.diverse_select(w, feats, cv, ck, ws=ws)[0].cpu().numpy()
         if kind in ("peaked", "huge"):
             assert (kept < 0).any(), f"{kind}: the matrix answered"
-        else:
+        elif max(lengths) <= 8192:
             assert np.array_equal(kept, want[0]), f"{kind}: the rounds answered"
 
 
